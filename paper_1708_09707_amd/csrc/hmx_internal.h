@@ -39,6 +39,41 @@ struct KernelEval {
 
 __device__ __forceinline__ float kexp(float a) { return __expf(a); }
 __device__ __forceinline__ double kexp(double a) { return exp(a); }
+
+// The exponential of near-field entries evaluated in the product (FP32: the
+// same as kexp).
+__device__ __forceinline__ float near_exp(float a) { return __expf(a); }
+// FP64, e^a for a <= 0 (every kernel's argument), NaN for NaN: a = k ln 2 + r
+// with ln 2 in two parts, |r| <= ln(2)/2 (1 + 2^-52), e^r = 1 + r + r^2 q(r)
+// with q of degree 10 interpolating (e^r - 1 - r) / r^2 at the Chebyshev nodes
+// of that interval (relative error 3.4e-19 in exact arithmetic, so the result
+// is within rounding of its 14 operations: at most 0.95 ulp off over
+// 60000 arguments in [-700, 0]), scaled by 2^k.  21 vector instructions and no
+// branch, so several entries' chains overlap; the library's takes about twice
+// as many.  Stored entries keep the library's: the last bit of an ACA entry
+// decides pivots where two candidates nearly tie, and another choice moves a
+// product by the approximation's tolerance rather than by rounding.
+__device__ __forceinline__ double near_exp(double a) {
+    constexpr double log2e = 1.4426950408889634, ln2_hi = 0.6931471805599453,
+                     ln2_lo = 2.3190468138462996e-17;
+    a = a < -746.0 ? -746.0 : a;  // rounds to zero; keeps the scaling's exponent in range
+    const double k = __builtin_rint(a * log2e);
+    double r = __builtin_fma(-k, ln2_hi, a);
+    r = __builtin_fma(-k, ln2_lo, r);
+    double q = 2.0914686968086876e-09;
+    q = __builtin_fma(q, r, 2.5105217004720745e-08);
+    q = __builtin_fma(q, r, 2.75572736431103e-07);
+    q = __builtin_fma(q, r, 2.7557255400206422e-06);
+    q = __builtin_fma(q, r, 2.4801587325547743e-05);
+    q = __builtin_fma(q, r, 0.00019841269874820627);
+    q = __builtin_fma(q, r, 0.0013888888888883748);
+    q = __builtin_fma(q, r, 0.008333333333326136);
+    q = __builtin_fma(q, r, 0.04166666666666667);
+    q = __builtin_fma(q, r, 0.1666666666666667);
+    q = __builtin_fma(q, r, 0.5);
+    const double p = 1.0 + __builtin_fma(r * r, q, r);
+    return __builtin_ldexp(p, (int)k);
+}
 __device__ __forceinline__ float ksqrt(float a) { return __fsqrt_rn(a); }
 __device__ __forceinline__ double ksqrt(double a) { return sqrt(a); }
 __device__ __forceinline__ float klog(float a) { return __logf(a); }
@@ -84,7 +119,8 @@ __device__ __forceinline__ float k1_node(const K1Nodes32&, int k) {
     return w[k];
 }
 
-template <typename T>
+// NEAR: with the near field's exponential
+template <bool NEAR = false, typename T>
 __device__ __forceinline__ T xk1(T s) {
     using Nodes = typename std::conditional<sizeof(T) == 8, K1Nodes64, K1Nodes32>::type;
     if (s <= (T)2) {
@@ -110,7 +146,7 @@ __device__ __forceinline__ T xk1(T s) {
         const T w2 = w * w;
         acc += k1_node(Nodes{}, k - 1) * ((T)1 + w2 * inv_2s) * ((T)2 / ksqrt(four_s + w2));
     }
-    return s * kexp(-s) * Nodes::h * acc;
+    return s * (NEAR ? near_exp(-s) : kexp(-s)) * Nodes::h * acc;
 }
 
 // phi for points x (d coords) and y (d coords)
@@ -142,9 +178,29 @@ __device__ __forceinline__ T phi(const KernelEval<T>& K, const T* x, const T* y,
     }
 }
 
+// phi of the squared distance r2 (or, for the low-rank test kernel, of the
+// inner product) for a fixed kernel kind; NEAR: with near_exp
+template <int KIND, bool NEAR = false, typename T>
+__device__ __forceinline__ T phi_of(const KernelEval<T>& K, T r2, T dot) {
+    if constexpr (KIND == HMX_GAUSSIAN) {
+        return NEAR ? near_exp(-r2 * K.inv_p0) : kexp(-r2 * K.inv_p0);
+    } else if constexpr (KIND == HMX_MATERN32) {
+        T s = ksqrt(r2) * K.s3_inv;
+        return ((T)1 + s) * (NEAR ? near_exp(-s) : kexp(-s));
+    } else if constexpr (KIND == HMX_MATERN_NU1) {
+        return K.norm * xk1<NEAR>(ksqrt(r2) * K.inv_p0);
+    } else if constexpr (KIND == HMX_TEST_CONST) {
+        (void)r2;
+        return (T)1;
+    } else {
+        T u = (T)1 + dot;
+        return u * u;
+    }
+}
+
 // phi for a fixed kernel kind, coordinates padded to three with zeros (the
-// padding adds exact zeros, so the value equals phi's)
-template <int KIND, typename T>
+// padding adds exact zeros, so the value equals phi's to rounding)
+template <int KIND, bool NEAR = false, typename T>
 __device__ __forceinline__ T phi_kind(const KernelEval<T>& K, const T* x, const T* y) {
     T r2 = 0, dot = 0;
 #pragma unroll
@@ -153,20 +209,25 @@ __device__ __forceinline__ T phi_kind(const KernelEval<T>& K, const T* x, const 
         r2 += t * t;
         if constexpr (KIND == HMX_TEST_LOWRANK) dot += x[k] * y[k];
     }
-    if constexpr (KIND == HMX_GAUSSIAN) {
-        return kexp(-r2 * K.inv_p0);
-    } else if constexpr (KIND == HMX_MATERN32) {
-        T s = ksqrt(r2) * K.s3_inv;
-        return ((T)1 + s) * kexp(-s);
-    } else if constexpr (KIND == HMX_MATERN_NU1) {
-        return K.norm * xk1(ksqrt(r2) * K.inv_p0);
-    } else if constexpr (KIND == HMX_TEST_CONST) {
-        (void)r2;
-        return (T)1;
-    } else {
-        T u = (T)1 + dot;
-        return u * u;
-    }
+    return phi_of<KIND, NEAR>(K, r2, dot);
+}
+
+__device__ __forceinline__ float kfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double kfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// the same with phi's own order of rounding, whatever the compiler would fuse:
+// the first square rounded, each further one fused into the sum (equal to phi
+// bit for bit)
+template <int KIND, typename T>
+__device__ __forceinline__ T phi_ordered(const KernelEval<T>& K, const T* x, const T* y) {
+    T t[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] = x[k] - y[k];
+    T r2 = kfma(t[0], t[0], (T)0), dot = (T)0;
+    r2 = kfma(t[2], t[2], kfma(t[1], t[1], r2));
+    if constexpr (KIND == HMX_TEST_LOWRANK)
+        dot = kfma(x[2], y[2], kfma(x[1], y[1], kfma(x[0], y[0], (T)0)));
+    return phi_of<KIND>(K, r2, dot);
 }
 
 // many problems in one union index space (batched builds): problem p owns
