@@ -331,9 +331,9 @@ struct hmx_graph_s {
 struct NpPlan {
     int64_t nl = 0, npcs = 0, nseg = 0;
     int64_t max_u = 0, max_v = 0, max_nb = 0;
-    int big_words = 0, med_words = 0, tiny_words = 0;  // the ACA classes' bitmask words
-    DevBuf blocks, lmap, cu, cv, rank, steps, spcs, seg_start, seg_tile;
-    std::vector<int64_t> bounds, hcu, hcv, cseg, cls;  // cls: nsplit, nbig, nmed per chunk
+    int big_words = 0;  // bitmask words of the largest single-workgroup block
+    DevBuf order, blocks, lmap, cu, cv, rank, steps, spcs, seg_start, seg_tile;
+    std::vector<int64_t> bounds, hcu, hcv, cseg, cls;  // cls: class bounds per chunk
 };
 
 struct hmx_hmatrix_s {
@@ -754,13 +754,12 @@ void stage_partition(hmx_hmatrix_s* h, const void* pts, int pts_f64, hipStream_t
     h->big_adm = big_adm;
 }
 
-// how the ACA treats the admissible leaves of a handle: size classes and
-// (learned sizing) the predicted targets
+// how the ACA treats the admissible leaves of a handle: which take the
+// many-workgroup path and (learned sizing) the predicted targets
 struct AcaPlan {
-    const int32_t* cls = nullptr;  // per leaf, non-decreasing; < split0: many workgroups,
-    int split0 = 0;                // < split: 512-thread class, < split2: 256-thread
-    int split = 0, split2 = 0;     // class, else single wave
-    int big_words = 2, med_words = 2, tiny_words = 2;  // LDS mask words per class
+    const int32_t* cls = nullptr;  // per leaf, non-decreasing; < split0: many workgroups
+    int split0 = 0;
+    int big_words = 2;  // LDS mask words of the largest single-workgroup block
     const int32_t* rt = nullptr;         // learned targets, or null
 };
 
@@ -772,23 +771,20 @@ struct AcaPlan {
 // default keeps the many-workgroup path for blocks whose bitmasks would not
 // fit a workgroup's LDS
 constexpr int64_t kDefaultSplitRows = (int64_t)1 << 18;
-// (one-wave class up to 512 points rather than 256: N = 2^22 3-d ACA
-// 3.36 -> 3.16 s, N = 2^20 2-d 38 -> 34.5 ms, the same ranks; the 512-thread
-// cut at 4096 or 8192 points makes no measurable difference)
+// (kBigRows and kTinyRows group the leaves of a batched handle; the ACA's own
+// size classes are cut by the blocks' sizes, kAcaClassRows)
 constexpr int64_t kBigRows = 4096;
 constexpr int64_t kTinyRows = 512;
 
-// size classes of a single problem by tree level: clusters at level l hold at
-// most s_l points (s_0 = n, s_{l+1} = ceil(s_l / 2)); levels whose clusters
-// can reach kBigRows points form the 512-thread class
 int64_t split_rows(const hmx_hmatrix_s* h) {
     return h->prm.aca_split_rows > 0 ? h->prm.aca_split_rows : kDefaultSplitRows;
 }
 
-// the first tree levels of the 512-thread, the 256-thread and the
-// single-wave class for a problem of n points (clusters at level l hold at
-// most ceil(n / 2^l) points); *s0, *s1, *s2: the largest cluster of each
-int4 level_cuts(int64_t n, int64_t split_at, int64_t* s0, int64_t* s1, int64_t* s2) {
+// the first tree levels below the many-workgroup path (c.x), below kBigRows
+// (c.y) and at most kTinyRows points (c.z) for a problem of n points (clusters
+// at level l hold at most ceil(n / 2^l) points); *s0: the largest cluster
+// below the many-workgroup path
+int4 level_cuts(int64_t n, int64_t split_at, int64_t* s0) {
     int4 c = make_int4(0, 0, 0, 0);
     int64_t a = n;  // the largest cluster below the many-workgroup levels
     while (a >= split_at) {
@@ -807,18 +803,14 @@ int4 level_cuts(int64_t n, int64_t split_at, int64_t* s0, int64_t* s1, int64_t* 
         ++c.z;
     }
     if (s0) *s0 = a;
-    if (s1) *s1 = b;
-    if (s2) *s2 = e;
     return c;
 }
 
 AcaPlan level_plan(const hmx_hmatrix_s* h) {
     AcaPlan p;
-    int64_t s0, s_split, s_split2;
-    const int4 c = level_cuts(h->n, split_rows(h), &s0, &s_split, &s_split2);
+    int64_t s0;
+    const int4 c = level_cuts(h->n, split_rows(h), &s0);
     p.split0 = c.x;
-    p.split = c.y;
-    p.split2 = c.z;
     const int64_t big = std::min(h->big_adm, s0);  // the largest single-workgroup block
     const int64_t words = 2 * ((big + 31) / 32);
     if (words * 4 > 64 * 1024) {
@@ -827,8 +819,6 @@ AcaPlan level_plan(const hmx_hmatrix_s* h) {
     }
     p.cls = h->adm_level.as<int32_t>();
     p.big_words = (int)std::max<int64_t>(words, 2);
-    p.med_words = (int)std::max<int64_t>(2 * ((std::min(s_split, big) + 31) / 32), 2);
-    p.tiny_words = (int)std::max<int64_t>(2 * ((std::min(s_split2, big) + 31) / 32), 2);
     return p;
 }
 
@@ -995,9 +985,26 @@ AcaArgs aca_args_base(const hmx_hmatrix_s* h, const AcaPlan& plan) {
     a.eps0 = h->prm.aca_eps0 >= 0 ? h->prm.aca_eps0 : (f64 ? 1e-14 : 1e-7);
     a.fixed = h->prm.rank_mode == HMX_RANK_FIXED;
     a.big_words = plan.big_words;
-    a.med_words = plan.med_words;
-    a.tiny_words = plan.tiny_words;
     return a;
+}
+
+// The blocks of a level-sorted chunk grouped by size class (stable): order
+// (nb entries) and the classes' bounds (kAcaClasses + 1 device entries)
+struct ClassSort {
+    DevBuf keys, scratch;
+};
+
+void class_order(ClassSort& cs, const int4* blocks, const int32_t* levels, int64_t nb, int lvl0,
+                 uint32_t* order, int64_t* bounds, hipStream_t st) {
+    if (!cs.keys.p || cs.keys.bytes < (size_t)nb * 8) {
+        if (cs.keys.p) check(hipStreamSynchronize(st), "class sort");
+        alloc(cs.keys, (size_t)nb * 8, "class keys");
+        alloc(cs.scratch, radix_sort_scratch_bytes(nb), "class sort");
+    }
+    check(launch_class_keys(blocks, levels, nb, lvl0, cs.keys.as<uint64_t>(), order, st),
+          "class keys");
+    check(radix_sort_pairs(cs.keys.as<uint64_t>(), order, nb, 8, cs.scratch.p, st), "class sort");
+    check(launch_class_bounds(cs.keys.as<uint64_t>(), nb, bounds, st), "class bounds");
 }
 
 // ACA scratch budget of one chunk, in compute-type entries: the caller's, else
@@ -1028,8 +1035,6 @@ void np_plan(hmx_hmatrix_s* h, const AcaPlan& plan, const int4* Lb, const int32_
     NpPlan& P = h->np;
     P.nl = nl;
     P.big_words = plan.big_words;
-    P.med_words = plan.med_words;
-    P.tiny_words = plan.tiny_words;
     const int kmax = h->prm.max_rank;
     DevBuf scan_scr;
     auto scan = [&](int64_t* data, int64_t cnt) -> int64_t {
@@ -1090,16 +1095,18 @@ void np_plan(hmx_hmatrix_s* h, const AcaPlan& plan, const int4* Lb, const int32_
     }
     // the size classes of every chunk (level-sorted within the chunk)
     DevBuf split;
-    alloc(split, (size_t)nch * 3 * 8, "class split");
-    check(hipMemsetAsync(split.p, 0, (size_t)nch * 3 * 8, st), "class split");
-    const int lv[3] = {plan.split0, plan.split, plan.split2};
-    for (int k = 0; k < nch; ++k)
-        for (int c = 0; c < 3; ++c)
-            check(launch_level_split(levels + P.bounds[k], P.bounds[k + 1] - P.bounds[k], lv[c],
-                                     split.as<int64_t>() + 3 * k + c, st),
-                  "class split");
-    P.cls.assign((size_t)nch * 3, 0);
-    d2h(P.cls.data(), split.p, (size_t)nch * 3 * 8, st);
+    alloc(P.order, (size_t)nl * 4, "class order");
+    alloc(split, (size_t)nch * (kAcaClasses + 1) * 8, "class bounds");
+    check(hipMemsetAsync(split.p, 0, (size_t)nch * (kAcaClasses + 1) * 8, st), "class bounds");
+    {
+        ClassSort cs;
+        for (int k = 0; k < nch; ++k)
+            class_order(cs, B + P.bounds[k], levels + P.bounds[k], P.bounds[k + 1] - P.bounds[k],
+                        plan.split0, P.order.as<uint32_t>() + P.bounds[k],
+                        split.as<int64_t>() + (kAcaClasses + 1) * k, st);
+        P.cls.assign((size_t)nch * (kAcaClasses + 1), 0);
+        d2h(P.cls.data(), split.p, P.cls.size() * 8, st);  // (before cs returns)
+    }
     P.max_u = P.max_v = P.max_nb = 0;
     for (int k = 0; k < nch; ++k) {
         P.max_u = std::max(P.max_u, P.hcu[k + 1] - P.hcu[k]);
@@ -1284,8 +1291,10 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
         const hipStream_t aux[3] = {auxs[0].s, auxs[1].s, auxs[2].s};
         const bool have_aux = aux[0] && aux[1] && aux[2];
         AcaArgs a = aca_args_base(h, plan);
-        DevBuf split;
-        alloc(split, 3 * 8, "class split");
+        ClassSort csort;
+        DevBuf order, split;
+        alloc(order, (size_t)nl * 4, "class order");
+        alloc(split, (kAcaClasses + 1) * 8, "class bounds");
 
         // one pass over blocks[0..nb): cap = per-block column capacity (null:
         // k_max), rt = one-shot targets (null: adaptive); exact offsets of the
@@ -1383,15 +1392,11 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
                 a.vbase = hcv[k];
                 a.rtarget = rt ? rt + b0 : nullptr;
                 // the size classes of this chunk (level-sorted within the chunk)
-                int64_t cls[3];
-                const int lv[3] = {plan.split0, plan.split, plan.split2};
-                for (int c = 0; c < 3; ++c)
-                    check(launch_level_split(levels + b0, nbk, lv[c], split.as<int64_t>() + c, st),
-                          "class split");
-                d2h(cls, split.p, sizeof cls, st);
-                a.nsplit = cls[0];
-                a.nbig = cls[1];
-                a.nmed = cls[2];
+                class_order(csort, a.blocks, levels + b0, nbk, plan.split0, order.as<uint32_t>(),
+                            split.as<int64_t>(), st);
+                d2h(a.cls, split.p, sizeof a.cls, st);
+                a.nsplit = a.cls[0];
+                a.order = order.as<uint32_t>();
                 a.rank = rank + b0;
                 a.steps = steps + b0;
                 a.ovf_u0 = hcu[k] + max_u;
@@ -2110,7 +2115,7 @@ void batched_impl(hmx_hmatrix_s* u, int np, const void* const* pts, int pts_f64,
         // ceil(max(n_1, n_2) / 2^l) points on either side)
         const int64_t nmax = cross ? std::max(n[0], n[1]) : 0;
         for (int p = 0; p < np; ++p)
-            cuts[p] = level_cuts(cross ? nmax : n[p], split_rows(u), nullptr, nullptr, nullptr);
+            cuts[p] = level_cuts(cross ? nmax : n[p], split_rows(u), nullptr);
         std::vector<int64_t> pb(u->offsets);
         DevBuf dcuts, dpb, keys, vals, sscr, big;
         alloc(dcuts, np * sizeof(int4), "class cuts");
@@ -2185,13 +2190,7 @@ void batched_impl(hmx_hmatrix_s* u, int np, const void* const* pts, int pts_f64,
         }
         plan.cls = cls.as<int32_t>();
         plan.split0 = 1;
-        plan.split = 2;
-        plan.split2 = 3;
         plan.big_words = (int)std::max<int64_t>(words, 2);
-        plan.med_words =
-            (int)std::max<int64_t>(2 * ((std::min(kBigRows - 1, big_rows) + 31) / 32), 2);
-        plan.tiny_words =
-            (int)std::max<int64_t>(2 * ((std::min(kTinyRows, big_rows) + 31) / 32), 2);
         plan.rt = learned ? rt.as<int32_t>() : nullptr;
     }
     stage_factors(u, plan, st, t_all);
@@ -2305,8 +2304,6 @@ void np_matvec(hmx_hmatrix_s* h, const void* x, void* z, double alpha, double be
     if (P.nl > 0) {
         AcaPlan plan{};
         plan.big_words = P.big_words;
-        plan.med_words = P.med_words;
-        plan.tiny_words = P.tiny_words;
         DevBuf Ucap, tb, t2b;
         const int64_t ucols = (std::max<int64_t>(P.max_u, 1) + 63) / 64 * 64;
         alloc(Ucap, (size_t)(ucols + std::max<int64_t>(P.max_v, 1)) * esz, "ACA chunk scratch");
@@ -2335,9 +2332,9 @@ void np_matvec(hmx_hmatrix_s* h, const void* x, void* z, double alpha, double be
             a.vbase = P.hcv[k];
             a.rank = rank + b0;
             a.steps = P.steps.as<int32_t>() + b0;
-            a.nsplit = P.cls[3 * k];
-            a.nbig = P.cls[3 * k + 1];
-            a.nmed = P.cls[3 * k + 2];
+            a.order = P.order.as<uint32_t>() + b0;
+            std::copy_n(&P.cls[(size_t)(kAcaClasses + 1) * k], kAcaClasses + 1, a.cls);
+            a.nsplit = a.cls[0];
             SplitBuffers sb;
             if (a.nsplit > 0) prepare_split(h, a, f64, st, sb);
             check(aca_classes_begin(a, f64, st, have_aux ? aux : nullptr), "aca");

@@ -352,7 +352,12 @@ hipError_t launch_iota_scan_tiles(int32_t* flags_to_tile, int64_t n, int32_t* ti
                                   int64_t* ntiles_dev, void* scratch, hipStream_t st);
 size_t tile_scan_scratch_bytes(int64_t n);
 
-// ACA (k_aca.hip)
+// ACA (k_aca.hip).  Size classes of the single-workgroup blocks by the larger
+// side's points: class c holds sides of at most kAcaClassRows[c] points (the
+// first class has no bound)
+constexpr int kAcaClasses = 8;
+__device__ constexpr int kAcaClassRows[kAcaClasses] = {0x7fffffff, 4096, 2048, 1024,
+                                                       512,        256,  128,  64};
 struct AcaArgs {
     const void* soa;      // d x n compute-type coords
     const double* soa64;  // d x n FP64 coords (first-column choice)
@@ -383,13 +388,20 @@ struct AcaArgs {
     void* V;
     int32_t* rank;
     int32_t* steps;
-    // size classes of the level-ordered list: [0, nsplit) many workgroups per
-    // block, [nsplit, nbig) 512-thread workgroups, [nbig, nmed) 256-thread
-    // ones, the rest (leaf levels) single-wave ones; each single-workgroup
-    // class reserves the used-row + used-col bitmask words of its largest block
-    int64_t nsplit, nbig, nmed;
-    int big_words, med_words, tiny_words;
+    // the blocks grouped by size: order[0 .. nblocks) holds block indices,
+    // [0, nsplit) (a prefix of the list, in place) run on many workgroups per
+    // block, [cls[c], cls[c + 1]) are size class c; big_words: used-row +
+    // used-column bitmask words of the list's largest single-workgroup block
+    const uint32_t* order;
+    int64_t nsplit;
+    int64_t cls[kAcaClasses + 1];
+    int big_words;
 };
+// stable grouping of a level-sorted chunk: keys for a sort of 8 bits, then
+// out[0 .. kAcaClasses]: first entries of the size classes and their end
+hipError_t launch_class_keys(const int4* blocks, const int32_t* level, int64_t nb, int lvl0,
+                             uint64_t* keys, uint32_t* vals, hipStream_t st);
+hipError_t launch_class_bounds(const uint64_t* keys, int64_t nb, int64_t* out, hipStream_t st);
 // queue the single-workgroup classes on aux[0..2] (3 streams, or null: all on
 // st) after the work queued on st; join makes st wait for them
 // chunking the ACA's level-ordered block list into slices that each hold a
@@ -433,9 +445,6 @@ size_t split_colpart_bytes(int f64);
 size_t split_rowpart_bytes(int f64);
 int split_tile();
 hipError_t launch_aca_split(const AcaArgs& a, const SplitPlan& p, int f64, hipStream_t st);
-// *out = first index with level[index] >= lvl in the non-decreasing level[0..nb)
-hipError_t launch_level_split(const int32_t* level, int64_t nb, int lvl, int64_t* out,
-                              hipStream_t st);
 
 // near field and matvec (k_mvp.hip)
 // A piece is the part of one leaf block inside one row tile (leaf cluster);
