@@ -176,20 +176,46 @@ struct DevBuf {
     }
 };
 
-// a second stream (default priority, non-blocking) owned for one build
+// A further stream (default priority, non-blocking) for the ACA's concurrent
+// classes, held by one build or product at a time.  Streams are returned idle to
+// a list per device that keeps at most kKeptStreams of them (the ones over it
+// are destroyed): creating and destroying three on each product without
+// precomputation took about 200 us of host time.
+constexpr size_t kKeptStreams = 12;
+std::mutex g_streams_mu;
+std::vector<std::pair<int, hipStream_t>> g_streams_free;  // (device, idle stream)
+
 struct AuxStream {
     hipStream_t s = nullptr;
+    int dev = 0;
     AuxStream() {
+        (void)hipGetDevice(&dev);
+        {
+            std::lock_guard<std::mutex> lk(g_streams_mu);
+            for (size_t i = g_streams_free.size(); i-- > 0;)
+                if (g_streams_free[i].first == dev) {
+                    s = g_streams_free[i].second;
+                    g_streams_free.erase(g_streams_free.begin() + (ptrdiff_t)i);
+                    return;
+                }
+        }
         if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
             (void)hipGetLastError();
             s = nullptr;  // the classes then run one after the other
         }
     }
     ~AuxStream() {
-        if (s) {
-            (void)hipStreamSynchronize(s);
-            (void)hipStreamDestroy(s);
+        if (!s) return;
+        // (after an error the stream may still hold work)
+        const bool idle = hipStreamSynchronize(s) == hipSuccess;
+        if (idle) {
+            std::lock_guard<std::mutex> lk(g_streams_mu);
+            if (g_streams_free.size() < kKeptStreams) {
+                g_streams_free.push_back({dev, s});
+                return;
+            }
         }
+        (void)hipStreamDestroy(s);
     }
     AuxStream(const AuxStream&) = delete;
     AuxStream& operator=(const AuxStream&) = delete;
@@ -2299,7 +2325,18 @@ void np_matvec(hmx_hmatrix_s* h, const void* x, void* z, double alpha, double be
     const int kmax = h->prm.max_rank;
     NpPlan& P = h->np;
     if (ev) check(hipEventRecord(ev[0], st), "event");
-    check(matvec_launch(h, x, z, alpha, beta, st, nullptr, h->rt_config), "matvec (near field)");
+    // The near field (and sigma2 x, beta z) needs nothing of the ACA: it is
+    // queued after the first chunk's classes have started on their streams, so
+    // its vector work fills the ACA's waits (events around the phases, or a
+    // first chunk with blocks on many workgroups, whose polls need st: before)
+    bool near_done = false;
+    auto near = [&] {
+        if (near_done) return;
+        near_done = true;
+        check(matvec_launch(h, x, z, alpha, beta, st, nullptr, h->rt_config),
+              "matvec (near field)");
+    };
+    if (ev || P.nl == 0) near();
     if (ev) check(hipEventRecord(ev[1], st), "event");
     if (P.nl > 0) {
         AcaPlan plan{};
@@ -2336,8 +2373,12 @@ void np_matvec(hmx_hmatrix_s* h, const void* x, void* z, double alpha, double be
             std::copy_n(&P.cls[(size_t)(kAcaClasses + 1) * k], kAcaClasses + 1, a.cls);
             a.nsplit = a.cls[0];
             SplitBuffers sb;
-            if (a.nsplit > 0) prepare_split(h, a, f64, st, sb);
+            if (a.nsplit > 0) {
+                near();
+                prepare_split(h, a, f64, st, sb);
+            }
             check(aca_classes_begin(a, f64, st, have_aux ? aux : nullptr), "aca");
+            near();
             if (a.nsplit > 0)
                 check(launch_aca_split(a, sb.P, f64, st), "aca (many workgroups per block)");
             check(aca_classes_join(st, have_aux ? aux : nullptr), "aca join");
@@ -2353,6 +2394,7 @@ void np_matvec(hmx_hmatrix_s* h, const void* x, void* z, double alpha, double be
                   "far field apply");
             if (a.nsplit > 0) check(hipStreamSynchronize(st), "chunk sync");  // sb returns
         }
+        near();
         if (ev) check(hipEventRecord(ev[2], st), "event");
         // the ranks of this product back to the leaves (a mirror takes its
         // primary's), and their statistics

@@ -11,11 +11,11 @@
 //               (sigma, tau) is another leaf, t'_b = U_b^T x|tau_b, since
 //               A|sigma x tau ~ V_b U_b^T), one workgroup per block;
 //   * np_apply: z|tau += alpha U_b t_b (and z|sigma += alpha V_b t'_b), one
-//               workgroup per row tile (leaf cluster) that the chunk's blocks
-//               touch, summing that tile's pieces in a fixed order, so the
-//               product is deterministic and needs no atomics: within one
-//               launch every tile is owned by one workgroup, and the chunks
-//               run one after the other.
+//               workgroup per 64 rows of a row tile (leaf cluster) that the
+//               chunk's blocks touch, summing that tile's pieces in a fixed
+//               order, so the product is deterministic and needs no atomics:
+//               within one launch every row is owned by one workgroup, and the
+//               chunks run one after the other.
 // The pieces (block, side) of each (chunk, tile) are sorted once at build
 // time: key = chunk * 2^tbits + tile, stable, so a tile's pieces keep the
 // list order, U side before the mirror side of the same block.
@@ -135,9 +135,34 @@ __global__ void np_chunk_segs_kernel(const uint64_t* __restrict__ keys,
     }
 }
 
-// t_b = V_b^T x|sigma (and t'_b = U_b^T x|tau for a mirrored primary): one
-// workgroup of four waves per block, a wave per column, lane-strided partial
-// sums combined by a butterfly (a fixed order)
+// sum_j col[j] x[j] over a wave: kTU loads of either in flight per lane, the
+// lanes' sums combined by a butterfly (a fixed order)
+constexpr int kTU = 8;
+
+template <typename T>
+__device__ __forceinline__ T column_dot(const T* __restrict__ col, const T* __restrict__ x, int len,
+                                        int lane) {
+    T s = 0;
+    int j = lane;
+    for (; j + (kTU - 1) * 64 < len; j += kTU * 64) {
+        T c[kTU], v[kTU];
+#pragma unroll
+        for (int u = 0; u < kTU; ++u) {
+            c[u] = col[j + u * 64];
+            v[u] = x[j + u * 64];
+        }
+#pragma unroll
+        for (int u = 0; u < kTU; ++u) s += c[u] * v[u];
+    }
+    for (; j < len; j += 64) s += col[j] * x[j];
+    return wave_sum(s);
+}
+
+// t_b = V_b^T x|sigma (and t'_b = U_b^T x|tau for a mirrored primary): a wave
+// per column, the columns of a block spread over gridDim.y workgroups of four
+// waves (a block's columns one after another on four waves left the chip to
+// the largest blocks: 428 us at N = 2^17, leaf 2048, rank 16, FP64, now
+// 96 us)
 template <typename T>
 __global__ __launch_bounds__(256) void np_t_kernel(const int4* __restrict__ blk, int64_t nbk,
                                                    const int32_t* __restrict__ rank,
@@ -148,25 +173,20 @@ __global__ __launch_bounds__(256) void np_t_kernel(const int4* __restrict__ blk,
                                                    const T* __restrict__ xm, int kmax, int sym,
                                                    T* __restrict__ t, T* __restrict__ t2) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int k0 = (int)blockIdx.y * 4 + w, ks = (int)gridDim.y * 4;
     for (int64_t q = blockIdx.x; q < nbk; q += gridDim.x) {
         const int4 b = blk[q];
         const int r = max(rank[q], 0);
         const int m = b.y - b.x, nn = b.w - b.z;
         const T* Vb = V + (cv[q] - vbase);
-        for (int k = w; k < r; k += 4) {
-            const T* col = Vb + (int64_t)k * nn;
-            T s = 0;
-            for (int j = lane; j < nn; j += 64) s += col[j] * xm[b.z + j];
-            s = wave_sum(s);
+        for (int k = k0; k < r; k += ks) {
+            const T s = column_dot(Vb + (int64_t)k * nn, xm + b.z, nn, lane);
             if (lane == 0) t[q * kmax + k] = s;
         }
         if (has_mirror(sym, b)) {
             const T* Ub = U + (cu[q] - ubase);
-            for (int k = w; k < r; k += 4) {
-                const T* col = Ub + (int64_t)k * m;
-                T s = 0;
-                for (int i = lane; i < m; i += 64) s += col[i] * xm[b.x + i];
-                s = wave_sum(s);
+            for (int k = k0; k < r; k += ks) {
+                const T s = column_dot(Ub + (int64_t)k * m, xm + b.x, m, lane);
                 if (lane == 0) t2[q * kmax + k] = s;
             }
         }
@@ -174,8 +194,16 @@ __global__ __launch_bounds__(256) void np_t_kernel(const int4* __restrict__ blk,
 }
 
 // z|tile += alpha sum over the tile's pieces of F_b(tile rows) t_b, one
-// workgroup per (chunk, tile) segment; q indexes the whole list, the
-// chunk's blocks start at b0 (t and t2 are chunk-local)
+// workgroup per (chunk, tile) segment and 64 rows of the tile: a lane per row,
+// the four waves taking the segment's pieces in turn (kAU columns' loads in
+// flight), their sums added in wave order; q indexes the whole list, the
+// chunk's blocks start at b0 (t and t2 are chunk-local).  A workgroup per
+// segment, its rows and pieces one after another, kept few compute units busy
+// on tall tiles and waited for one entry at a time: 1958 us at N = 2^17, leaf
+// 2048, rank 16, FP64; now 117 us.
+constexpr int kAU = 8;
+constexpr int kApplyRows = 64;
+
 template <typename T>
 __global__ __launch_bounds__(256) void np_apply_kernel(
     const int64_t* __restrict__ seg_start, const int32_t* __restrict__ seg_tile, int64_t s0,
@@ -185,13 +213,18 @@ __global__ __launch_bounds__(256) void np_apply_kernel(
     const T* __restrict__ U, const T* __restrict__ V, const T* __restrict__ t,
     const T* __restrict__ t2, int kmax, const int32_t* __restrict__ tile_lo,
     const int32_t* __restrict__ perm, T alpha, T* __restrict__ z) {
+    __shared__ T part[4][kApplyRows];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int64_t s = s0 + blockIdx.x; s < s0 + ns; s += gridDim.x) {
         const int tile = seg_tile[s];
         const int r0 = tile_lo[tile], r1 = tile_lo[tile + 1];
         const int64_t p0 = seg_start[s], p1 = seg_start[s + 1];
-        for (int row = r0 + (int)threadIdx.x; row < r1; row += blockDim.x) {
+        // (the same trip count for every thread of the workgroup)
+        for (int rb = r0 + (int)blockIdx.y * kApplyRows; rb < r1;
+             rb += (int)gridDim.y * kApplyRows) {
+            const int row = rb + lane < r1 ? rb + lane : r1 - 1;
             T acc = 0;
-            for (int64_t p = p0; p < p1; ++p) {
+            for (int64_t p = p0 + w; p < p1; p += 4) {
                 const int2 pc = spcs[p];
                 const int4 b = blk[pc.x];
                 const int r = max(rank[pc.x], 0);
@@ -207,10 +240,27 @@ __global__ __launch_bounds__(256) void np_apply_kernel(
                     F = V + (cv[pc.x] - vbase) + (row - b.z);
                     tv = t2 + (pc.x - b0) * kmax;
                 }
-                for (int k = 0; k < r; ++k) acc += F[k * ld] * tv[k];
+                int k = 0;
+                for (; k + kAU <= r; k += kAU) {
+                    T f[kAU], c[kAU];
+#pragma unroll
+                    for (int u = 0; u < kAU; ++u) {
+                        f[u] = F[(k + u) * ld];
+                        c[u] = tv[k + u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAU; ++u) acc += f[u] * c[u];
+                }
+                for (; k < r; ++k) acc += F[k * ld] * tv[k];
             }
-            const int64_t o = perm[row];
-            z[o] = z[o] + alpha * acc;
+            part[w][lane] = acc;
+            __syncthreads();
+            if (w == 0 && rb + lane < r1) {
+                const T sum = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+                const int64_t o = perm[row];
+                z[o] = z[o] + alpha * sum;
+            }
+            __syncthreads();
         }
     }
 }
@@ -269,13 +319,16 @@ hipError_t launch_np_t(const int4* blk, int64_t nbk, const int32_t* rank, const 
                        const void* V, const void* xm, int kmax, int sym, void* t, void* t2,
                        int f64, hipStream_t st) {
     if (nbk <= 0) return hipSuccess;
-    const unsigned g = (unsigned)std::min<int64_t>(nbk, 1 << 20);
+    // up to 16 columns of a block side by side (more are taken in turn); a
+    // long list fills the chip with a workgroup a block
+    const unsigned gy = nbk >= (1 << 14) ? 1u : (unsigned)std::min((kmax + 3) / 4, 4);
+    const dim3 g((unsigned)std::min<int64_t>(nbk, 1 << 20), gy);
     if (f64)
-        hipLaunchKernelGGL(np_t_kernel<double>, dim3(g), dim3(256), 0, st, blk, nbk, rank, cu, cv,
+        hipLaunchKernelGGL(np_t_kernel<double>, g, dim3(256), 0, st, blk, nbk, rank, cu, cv,
                            ubase, vbase, (const double*)U, (const double*)V, (const double*)xm,
                            kmax, sym, (double*)t, (double*)t2);
     else
-        hipLaunchKernelGGL(np_t_kernel<float>, dim3(g), dim3(256), 0, st, blk, nbk, rank, cu, cv,
+        hipLaunchKernelGGL(np_t_kernel<float>, g, dim3(256), 0, st, blk, nbk, rank, cu, cv,
                            ubase, vbase, (const float*)U, (const float*)V, (const float*)xm, kmax,
                            sym, (float*)t, (float*)t2);
     return hipGetLastError();
@@ -289,15 +342,15 @@ hipError_t launch_np_apply(const int64_t* seg_start, const int32_t* seg_tile, in
                            const int32_t* perm, double alpha, void* z, int max_tile, int f64,
                            hipStream_t st) {
     if (ns <= 0) return hipSuccess;
-    const unsigned g = (unsigned)std::min<int64_t>(ns, 1 << 20);
-    const int nt = (int)std::min<int64_t>(256, std::max<int64_t>(64, (max_tile + 63) / 64 * 64));
+    const dim3 g((unsigned)std::min<int64_t>(ns, 1 << 20),
+                 (unsigned)std::min<int64_t>((max_tile + kApplyRows - 1) / kApplyRows, 1 << 10));
     if (f64)
-        hipLaunchKernelGGL(np_apply_kernel<double>, dim3(g), dim3(nt), 0, st, seg_start, seg_tile,
+        hipLaunchKernelGGL(np_apply_kernel<double>, g, dim3(256), 0, st, seg_start, seg_tile,
                            s0, ns, spcs, blk, rank, cu, cv, ubase, vbase, b0, (const double*)U,
                            (const double*)V, (const double*)t, (const double*)t2, kmax, tile_lo,
                            perm, alpha, (double*)z);
     else
-        hipLaunchKernelGGL(np_apply_kernel<float>, dim3(g), dim3(nt), 0, st, seg_start, seg_tile,
+        hipLaunchKernelGGL(np_apply_kernel<float>, g, dim3(256), 0, st, seg_start, seg_tile,
                            s0, ns, spcs, blk, rank, cu, cv, ubase, vbase, b0, (const float*)U,
                            (const float*)V, (const float*)t, (const float*)t2, kmax, tile_lo,
                            perm, (float)alpha, (float*)z);
