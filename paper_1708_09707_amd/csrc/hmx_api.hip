@@ -341,7 +341,7 @@ double ms_since(std::chrono::steady_clock::time_point t0) {
 struct hmx_mlp_s {
     DevBuf w, m, v, mean, scale;
     int64_t t = 0;  // Adam steps taken
-    DevBuf act, scratch, grad, Xb, yb, loss;
+    DevBuf act, scratch, grad, Xb, yb, loss;  // (act: outputs that overlap their inputs)
 };
 
 // a captured sequence of matvecs (hmx_matvec_graph)
@@ -3534,13 +3534,15 @@ hmx_status hmx_mlp_forward(hmx_mlp m, const float* X, int64_t B, float* out, voi
     if (B == 0) return HMX_OK;
     hipStream_t st = (hipStream_t)stream;
     return guarded([&] {
-        ensure(m->act, (size_t)B * 193 * 4, st, "activations");
-        check(mlp_forward(m->w.as<float>(), m->mean.as<float>(), m->scale.as<float>(), X, B,
-                          m->act.as<float>(), st),
+        // an output that overlaps the features goes through a buffer
+        const bool apart = out + B <= X || X + (size_t)B * 8 <= out;
+        if (!apart) ensure(m->act, (size_t)B * 4, st, "outputs");
+        float* const o = apart ? out : m->act.as<float>();
+        check(mlp_forward(m->w.as<float>(), m->mean.as<float>(), m->scale.as<float>(), X, B, o, st),
               "mlp forward");
-        check(hipMemcpyAsync(out, m->act.as<float>() + (size_t)B * 192, (size_t)B * 4,
-                             hipMemcpyDeviceToDevice, st),
-              "output copy");
+        if (!apart)
+            check(hipMemcpyAsync(out, o, (size_t)B * 4, hipMemcpyDeviceToDevice, st),
+                  "output copy");
     });
 }
 
@@ -3549,14 +3551,10 @@ namespace {
 // forward + backward on a device batch; loss_dev optional
 void mlp_step_grad(hmx_mlp_s* m, const float* X, const float* y, int64_t B, double q,
                    float* grad, double* loss_dev, hipStream_t st) {
-    ensure(m->act, (size_t)B * 193 * 4, st, "activations");
-    ensure(m->scratch, mlp_grad_scratch_floats(B) * 4, st, "gradient scratch");
-    check(mlp_forward(m->w.as<float>(), m->mean.as<float>(), m->scale.as<float>(), X, B,
-                      m->act.as<float>(), st),
-          "mlp forward");
-    check(mlp_backward(m->w.as<float>(), m->mean.as<float>(), m->scale.as<float>(), X, y, B,
-                       (float)q, m->act.as<float>(), grad, m->scratch.as<float>(), loss_dev, st),
-          "mlp backward");
+    ensure(m->scratch, mlp_grad_scratch_bytes(B), st, "gradient scratch");
+    check(mlp_loss_grad(m->w.as<float>(), m->mean.as<float>(), m->scale.as<float>(), X, y, B,
+                        (float)q, grad, m->scratch.p, loss_dev, st),
+          "mlp loss and gradient");
 }
 }  // namespace
 }  // extern "C++"
@@ -3603,8 +3601,7 @@ hmx_status hmx_mlp_train(hmx_mlp m, const float* X, const float* y, int64_t n,
         ensure(m->Xb, (size_t)B * 8 * 4, st, "batch features");
         ensure(m->yb, (size_t)B * 4, st, "batch targets");
         ensure(m->grad, (size_t)kP * 4, st, "gradient");
-        ensure(m->act, (size_t)B * 193 * 4, st, "activations");
-        ensure(m->scratch, mlp_grad_scratch_floats(B) * 4, st, "gradient scratch");
+        ensure(m->scratch, mlp_grad_scratch_bytes(B), st, "gradient scratch");
         for (int32_t s = 0; s < steps; ++s) {
             check(mlp_gather_batch(X, y, n, batch_idx + (int64_t)s * B, B, m->Xb.as<float>(),
                                    m->yb.as<float>(), st),

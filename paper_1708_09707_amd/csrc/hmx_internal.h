@@ -547,13 +547,12 @@ hipError_t launch_sub(void* out, const void* a, const void* b, int64_t n, int f6
 
 // learned rank sizing (k_mlp.hip): MLP 8 -> 64 -> 64 -> 64 -> 1 (ReLU), FP32
 int64_t mlp_nparams();
-size_t mlp_grad_scratch_floats(int64_t B);
-// act: B * (3 * 64 + 1) floats (hidden activations, then the outputs)
 hipError_t mlp_forward(const float* w, const float* mean, const float* scale, const float* X,
-                       int64_t B, float* act, hipStream_t st);
-hipError_t mlp_backward(const float* w, const float* mean, const float* scale, const float* X,
-                        const float* y, int64_t B, float q, const float* act, float* grad,
-                        float* scratch, double* loss, hipStream_t st);
+                       int64_t B, float* out, hipStream_t st);
+size_t mlp_grad_scratch_bytes(int64_t B);
+hipError_t mlp_loss_grad(const float* w, const float* mean, const float* scale, const float* X,
+                         const float* y, int64_t B, float q, float* grad, void* scratch,
+                         double* loss, hipStream_t st);
 hipError_t mlp_adam(float* w, float* m, float* v, const float* g, int64_t t, float lr, float b1,
                     float b2, float eps, hipStream_t st);
 hipError_t mlp_norm(const float* X, int64_t n, float* mean, float* scale, hipStream_t st);

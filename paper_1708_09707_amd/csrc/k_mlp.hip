@@ -5,8 +5,8 @@
 // Parameters are one float array packed as W1 (64x8, row-major), b1, W2
 // (64x64), b2, W3 (64x64), b3, W4 (1x64), b4.  Inputs are standardised with a
 // fixed per-feature mean / scale.  Training minimises the pinball (quantile)
-// loss with Adam.  Every kernel maps one thread to one output element and
-// sums in a fixed order, so forward, backward and updates are deterministic.
+// loss with Adam.  Every sum has a fixed order, so forward, backward and updates
+// are deterministic.
 #include "hmx_internal.h"
 
 namespace hmx {
@@ -19,90 +19,239 @@ constexpr int64_t kOffW1 = 0, kOffB1 = kOffW1 + kH * kIn, kOffW2 = kOffB1 + kH,
                   kOffB2 = kOffW2 + kH * kH, kOffW3 = kOffB2 + kH, kOffB3 = kOffW3 + kH * kH,
                   kOffW4 = kOffB3 + kH, kOffB4 = kOffW4 + kH, kNParam = kOffB4 + 1;
 
-// Y[b, i] = act(sum_k W[i, k] X[b, k] + bias[i]) (X rows of length in, Y of out)
-__global__ void layer_fwd_kernel(const float* __restrict__ X, int64_t B, int in, int out,
-                                 const float* __restrict__ W, const float* __restrict__ bias,
-                                 int relu, const float* __restrict__ mean,
-                                 const float* __restrict__ scale, float* __restrict__ Y) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= B * out) return;
-    const int64_t b = e / out;
-    const int i = (int)(e - b * out);
-    float s = bias[i];
-    const float* x = X + b * in;
-    for (int k = 0; k < in; ++k) {
-        const float xv = mean ? (x[k] - mean[k]) * scale[k] : x[k];
-        s += W[(int64_t)i * in + k] * xv;
+// Forward, and with GRAD forward, loss and backward, of tiles of 64 samples in
+// one kernel (eight waves, a tile's activations and deltas in LDS, transposed:
+// row k holds unit k of the 64 samples).
+//   * Forward layers: a lane per sample, eight outputs a wave, the weights in
+//     scalar registers; each output is its bias plus the products in unit
+//     order, in the vector units (the prediction decides the side of the
+//     pinball loss, and keeps the bits of that order).
+//   * Backward: the 64 x 64 x 64 contractions dZ' = W^T dZ and gW = dZ A^T on the
+//     16x16x4 FP32 matrix instructions; the weight gradients accumulate in
+//     registers over a workgroup's tiles and leave it once, as one row of
+//     part, which grad_reduce_kernel adds in order.
+// Bound by latency: a tile is about 25 us of work of one compute unit whatever
+// the batch, up to 64 x kMlpGroups samples.  B = 16384: the forward pass 276 us as
+// four launches of a thread per output, now 12 us; loss and gradient 860 us
+// as 17 launches, now 33 us.
+constexpr int kMT = 64;            // samples per tile
+constexpr int kMP = kMT + 4;       // row stride of a tile: 4 i + g over all 64 banks
+constexpr int kMW = 8;             // waves
+constexpr int kMlpGroups = 256;    // workgroups (rows of part) at most
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+struct MlpTile {
+    float x[kIn * kMP];
+    float a1[kH * kMP], a2[kH * kMP], a3[kH * kMP];
+    float d0[kH * kMP], d1[kH * kMP];
+    float dout[kMT];
+};
+
+// out row i = relu(bias_i + sum_k W[i, k] in row k), eight rows a wave
+template <int IN>
+__device__ __forceinline__ void tile_layer(const float* __restrict__ W, const float* __restrict__ bias,
+                                           const float* in, float* out, int wave, int lane) {
+    const int i0 = wave * 8;
+    float s[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s[u] = bias[i0 + u];
+#pragma unroll 8
+    for (int k = 0; k < IN; ++k) {
+        const float x = in[k * kMP + lane];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s[u] = __builtin_fmaf(W[(i0 + u) * IN + k], x, s[u]);
     }
-    Y[e] = relu ? (s > 0.f ? s : 0.f) : s;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) out[(i0 + u) * kMP + lane] = s[u] > 0.f ? s[u] : 0.f;
 }
 
-// pinball loss: dout[b] = -(q - [y - o < 0]) / B, lpart[b] = rho_q(y - o)
-__global__ void loss_kernel(const float* __restrict__ o, const float* __restrict__ y, int64_t B,
-                            float q, float* __restrict__ dout, float* __restrict__ lpart) {
-    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const float u = y[b] - o[b];
-    const float ind = u < 0.f ? 1.f : 0.f;
-    dout[b] = -(q - ind) / (float)B;
-    lpart[b] = u * (q - ind);
+// dp row k = [a row k > 0] sum_j W[j, k] d row j: wave w forms rows 16 (w / 2)
+// .. + 15 of samples 32 (w % 2) .. + 31
+__device__ __forceinline__ void tile_delta(const float* __restrict__ W, const float* d,
+                                           const float* a, float* dp, int wave, int lane) {
+    const int k0 = (wave >> 1) * 16, b0 = (wave & 1) * 32, l = lane & 15, g = lane >> 4;
+    f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+#pragma unroll 4
+    for (int j = 0; j < kH; j += 4) {
+        const float wv = W[(j + g) * kH + k0 + l];
+        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv, d[(j + g) * kMP + b0 + l], c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv, d[(j + g) * kMP + b0 + 16 + l], c1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int e = (k0 + 4 * g + v) * kMP + b0 + l;
+        dp[e] = a[e] > 0.f ? c0[v] : 0.f;
+        dp[e + 16] = a[e + 16] > 0.f ? c1[v] : 0.f;
+    }
 }
 
-// dZ[b, k] = [A[b, k] > 0] * sum_j W[j, k] dN[b, j]  (W: next layer, nout x nin)
-__global__ void delta_kernel(const float* __restrict__ dN, const float* __restrict__ W,
-                             const float* __restrict__ A, int64_t B, int nin, int nout,
-                             float* __restrict__ dZ) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= B * nin) return;
-    const int64_t b = e / nin;
-    const int k = (int)(e - b * nin);
+// acc += rows 16 (w / 2) .. of d times rows 32 (w % 2) .. + 31 of a, summed over
+// the samples: gW[i, k] += sum_b d[i, b] a[k, b]
+__device__ __forceinline__ void tile_wgrad(const float* d, const float* a, f32x4 (&acc)[2], int wave,
+                                           int lane) {
+    const int i0 = (wave >> 1) * 16, k0 = (wave & 1) * 32, l = lane & 15, g = lane >> 4;
+#pragma unroll 4
+    for (int b = 0; b < kMT; b += 4) {
+        const float dv = d[(i0 + l) * kMP + b + g];
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv, a[(k0 + l) * kMP + b + g], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv, a[(k0 + 16 + l) * kMP + b + g], acc[1], 0,
+                                                     0, 0);
+    }
+}
+
+// this thread's eighth of sum_b d[i, b] f[b] (f null: 1), i = thread / 8: the
+// eight threads of a row hold its total afterwards
+__device__ __forceinline__ float tile_row_sum(const float* d, const float* f, int tid) {
+    const float* r = d + (tid >> 3) * kMP;
     float s = 0.f;
-    for (int j = 0; j < nout; ++j) s += W[(int64_t)j * nin + k] * dN[b * nout + j];
-    dZ[e] = A[e] > 0.f ? s : 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int b = (tid & 7) + 8 * q;
+        s += f ? r[b] * f[b] : r[b];
+    }
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    s += __shfl_xor(s, 4, 64);
+    return s;
 }
 
-// Weight gradients in two passes with a fixed summation order: pass 1 gives
-// every chunk of kGradChunk samples its partial sums
-//   part[c, i * (in + 1) + k] = sum_{b in chunk c} dZ[b, i] X[b, k]   (k < in)
-//   part[c, i * (in + 1) + in] = sum_{b in chunk c} dZ[b, i]
-// and pass 2 adds the chunks in order into gW (out x in) and gbias (out).
-constexpr int kGradChunk = 256;
-
-__global__ void wgrad_partial_kernel(const float* __restrict__ dZ, const float* __restrict__ X,
-                                     int64_t B, int in, int out, const float* __restrict__ mean,
-                                     const float* __restrict__ scale, float* __restrict__ part) {
-    const int P = out * (in + 1);
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t c = blockIdx.y;
-    if (e >= P) return;
-    const int i = e / (in + 1), k = e - i * (in + 1);
-    const int64_t b0 = c * kGradChunk;
-    const int64_t b1 = b0 + kGradChunk < B ? b0 + kGradChunk : B;
-    float s = 0.f;
-    if (k < in) {
-        const float mu = mean ? mean[k] : 0.f, sc = mean ? scale[k] : 1.f;
-        for (int64_t b = b0; b < b1; ++b) {
-            const float xv = mean ? (X[b * in + k] - mu) * sc : X[b * in + k];
-            s += dZ[b * out + i] * xv;
+// part: gridDim.x rows of kNParam gradients; lpart: their loss sums (FP64)
+template <bool GRAD>
+__global__ __launch_bounds__(kMW * 64) void mlp_tile_kernel(
+    const float* __restrict__ X, const float* __restrict__ y, int64_t B, float q,
+    const float* __restrict__ w, const float* __restrict__ mean, const float* __restrict__ scale,
+    float* __restrict__ out, float* __restrict__ part, double* __restrict__ lpart) {
+    extern __shared__ __align__(16) unsigned char mlp_lds[];
+    MlpTile& T = *reinterpret_cast<MlpTile*>(mlp_lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l = lane & 15, g = lane >> 4;
+    const int64_t ntiles = (B + kMT - 1) / kMT;
+    f32x4 g1 = {0.f, 0.f, 0.f, 0.f}, g2[2] = {g1, g1}, g3[2] = {g1, g1};
+    float b1 = 0.f, b2 = 0.f, b3 = 0.f, g4 = 0.f, b4 = 0.f;  // rows tid / 8
+    double lsum = 0.0;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int64_t s0 = t * kMT;
+        {
+            const int b = tid >> 3, k = tid & 7;
+            const int64_t sb = s0 + b;
+            T.x[k * kMP + b] = sb < B ? (X[sb * kIn + k] - mean[k]) * scale[k] : 0.f;
         }
-    } else {
-        for (int64_t b = b0; b < b1; ++b) s += dZ[b * out + i];
+        __syncthreads();
+        tile_layer<kIn>(w + kOffW1, w + kOffB1, T.x, T.a1, wave, lane);
+        __syncthreads();
+        tile_layer<kH>(w + kOffW2, w + kOffB2, T.a1, T.a2, wave, lane);
+        __syncthreads();
+        tile_layer<kH>(w + kOffW3, w + kOffB3, T.a2, T.a3, wave, lane);
+        __syncthreads();
+        if (wave == 0) {
+            float o = w[kOffB4];
+#pragma unroll 8
+            for (int k = 0; k < kH; ++k)
+                o = __builtin_fmaf(w[kOffW4 + k], T.a3[k * kMP + lane], o);
+            const bool in = s0 + lane < B;
+            if constexpr (GRAD) {
+                // pinball loss rho_q(y - o) and its derivative by o over B
+                const float u = in ? y[s0 + lane] - o : 0.f;
+                const float ind = u < 0.f ? 1.f : 0.f;
+                T.dout[lane] = in ? -(q - ind) / (float)B : 0.f;
+                if (in) lsum += u * (q - ind);
+            } else if (in) {
+                out[s0 + lane] = o;
+            }
+        }
+        __syncthreads();
+        if constexpr (GRAD) {
+            // output layer, and the deltas of the third
+            g4 += tile_row_sum(T.a3, T.dout, tid);
+            if (tid < 64) {
+                float s = T.dout[lane];
+#pragma unroll
+                for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
+                b4 += s;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = wave * 8 + u;
+                T.d0[k * kMP + lane] =
+                    T.a3[k * kMP + lane] > 0.f ? w[kOffW4 + k] * T.dout[lane] : 0.f;
+            }
+            __syncthreads();
+            tile_wgrad(T.d0, T.a2, g3, wave, lane);
+            b3 += tile_row_sum(T.d0, nullptr, tid);
+            tile_delta(w + kOffW3, T.d0, T.a2, T.d1, wave, lane);
+            __syncthreads();
+            tile_wgrad(T.d1, T.a1, g2, wave, lane);
+            b2 += tile_row_sum(T.d1, nullptr, tid);
+            tile_delta(w + kOffW2, T.d1, T.a1, T.d0, wave, lane);
+            __syncthreads();
+            b1 += tile_row_sum(T.d0, nullptr, tid);
+            if (wave < 4) {  // 64 x 8: the lanes of inputs 8 .. 15 repeat input 7
+#pragma unroll 4
+                for (int b = 0; b < kMT; b += 4)
+                    g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        T.d0[(wave * 16 + l) * kMP + b + g],
+                        T.x[(l < kIn ? l : kIn - 1) * kMP + b + g], g1, 0, 0, 0);
+            }
+            __syncthreads();  // the tile's rows are refilled by the next
+        }
     }
-    part[c * P + e] = s;
+    if constexpr (GRAD) {
+        float* __restrict__ P = part + (int64_t)blockIdx.x * kNParam;
+        const int i0 = (wave >> 1) * 16, k0 = (wave & 1) * 32;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = i0 + 4 * g + v;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                P[kOffW2 + i * kH + k0 + 16 * h + l] = g2[h][v];
+                P[kOffW3 + i * kH + k0 + 16 * h + l] = g3[h][v];
+            }
+            if (wave < 4 && l < kIn) P[kOffW1 + (wave * 16 + 4 * g + v) * kIn + l] = g1[v];
+        }
+        if ((tid & 7) == 0) {
+            const int i = tid >> 3;
+            P[kOffB1 + i] = b1;
+            P[kOffB2 + i] = b2;
+            P[kOffB3 + i] = b3;
+            P[kOffW4 + i] = g4;
+        }
+        if (wave == 0) {
+            lsum = wave_sum(lsum);
+            if (lane == 0) {
+                P[kOffB4] = b4;
+                lpart[blockIdx.x] = lsum;
+            }
+        }
+    }
 }
 
-__global__ void wgrad_reduce_kernel(const float* __restrict__ part, int64_t nchunks, int in,
-                                    int out, float* __restrict__ gW, float* __restrict__ gb) {
-    const int P = out * (in + 1);
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= P) return;
+// grad[p] = the rows of part summed (each wave a quarter of them in order, the
+// four added in order), *loss = the loss sums over B
+__global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restrict__ part,
+                                                          const double* __restrict__ lpart,
+                                                          int rows, int64_t B,
+                                                          float* __restrict__ grad,
+                                                          double* __restrict__ loss) {
+    __shared__ float sh[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + lane;
+    const int per = (rows + 3) / 4, r0 = w * per, r1 = r0 + per < rows ? r0 + per : rows;
     float s = 0.f;
-    for (int64_t c = 0; c < nchunks; ++c) s += part[c * P + e];
-    const int i = e / (in + 1), k = e - i * (in + 1);
-    if (k < in)
-        gW[(int64_t)i * in + k] = s;
-    else
-        gb[i] = s;
+    if (p < kNParam) {
+#pragma unroll 8
+        for (int r = r0; r < r1; ++r) s += part[(int64_t)r * kNParam + p];
+    }
+    sh[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && p < kNParam) grad[p] = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
+    if (blockIdx.x == 0 && w == 1 && loss) {
+        double t = 0.0;
+        for (int r = lane; r < rows; r += 64) t += lpart[r];
+        t = wave_sum(t);
+        if (lane == 0) *loss = t / (double)B;
+    }
 }
 
 // Adam step t >= 1 on n parameters (bias-corrected), FP32
@@ -117,18 +266,6 @@ __global__ void adam_kernel(float* __restrict__ w, float* __restrict__ m, float*
     m[i] = mi;
     v[i] = vi;
     w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
-// *out = mean of a[0..n), accumulated in FP64 (one workgroup, fixed tree)
-__global__ void sum_kernel(const float* __restrict__ a, int64_t n, double* __restrict__ out) {
-    if (blockIdx.x != 0) return;
-    __shared__ double sh[4];
-    double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) acc += a[i];
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) *out = (sh[0] + sh[1] + sh[2] + sh[3]) / (double)n;
 }
 
 // per-feature mean and 1 / std over n samples (FP64 sums, one workgroup per feature)
@@ -333,72 +470,41 @@ unsigned g1d(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 int64_t mlp_nparams() { return kNParam; }
 
-// activations: buffer of B * (3 * 64 + 1) floats
-hipError_t mlp_forward(const float* w, const float* mean, const float* scale, const float* X,
-                       int64_t B, float* act, hipStream_t st) {
-    if (B == 0) return hipSuccess;
-    float* A1 = act;
-    float* A2 = A1 + B * kH;
-    float* A3 = A2 + B * kH;
-    float* O = A3 + B * kH;
-    hipLaunchKernelGGL(layer_fwd_kernel, dim3(g1d(B * kH)), dim3(256), 0, st, X, B, kIn, kH,
-                       w + kOffW1, w + kOffB1, 1, mean, scale, A1);
-    hipLaunchKernelGGL(layer_fwd_kernel, dim3(g1d(B * kH)), dim3(256), 0, st, A1, B, kH, kH,
-                       w + kOffW2, w + kOffB2, 1, nullptr, nullptr, A2);
-    hipLaunchKernelGGL(layer_fwd_kernel, dim3(g1d(B * kH)), dim3(256), 0, st, A2, B, kH, kH,
-                       w + kOffW3, w + kOffB3, 1, nullptr, nullptr, A3);
-    hipLaunchKernelGGL(layer_fwd_kernel, dim3(g1d(B)), dim3(256), 0, st, A3, B, kH, 1, w + kOffW4,
-                       w + kOffB4, 0, nullptr, nullptr, O);
-    return hipGetLastError();
-}
-
-size_t mlp_grad_scratch_floats(int64_t B) {
-    const int64_t nch = (B + kGradChunk - 1) / kGradChunk;
-    return (size_t)(B * (3 * kH + 2) + nch * kH * (kH + 1));
-}
-
 namespace {
-void wgrad(const float* dZ, const float* X, int64_t B, int in, int out, const float* mean,
-           const float* scale, float* part, float* gW, float* gb, hipStream_t st) {
-    const int P = out * (in + 1);
-    const int64_t nch = (B + kGradChunk - 1) / kGradChunk;
-    hipLaunchKernelGGL(wgrad_partial_kernel, dim3(g1d(P), (unsigned)nch), dim3(256), 0, st, dZ, X,
-                       B, in, out, mean, scale, part);
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(g1d(P)), dim3(256), 0, st, part, nch, in, out, gW,
-                       gb);
+unsigned mlp_groups(int64_t B) {
+    const int64_t t = (B + kMT - 1) / kMT;
+    return (unsigned)(t < kMlpGroups ? t : kMlpGroups);
 }
 }  // namespace
 
-// gradient of the mean pinball loss over the batch (act from mlp_forward on
-// the same batch); scratch: mlp_grad_scratch_floats(B) floats; loss (device
-// double) optional
-hipError_t mlp_backward(const float* w, const float* mean, const float* scale, const float* X,
-                        const float* y, int64_t B, float q, const float* act, float* grad,
-                        float* scratch, double* loss, hipStream_t st) {
+// out[b] for the B samples of X (which must not overlap out)
+hipError_t mlp_forward(const float* w, const float* mean, const float* scale, const float* X,
+                       int64_t B, float* out, hipStream_t st) {
     if (B == 0) return hipSuccess;
-    const float* A1 = act;
-    const float* A2 = A1 + B * kH;
-    const float* A3 = A2 + B * kH;
-    const float* O = A3 + B * kH;
-    float* dO = scratch;
-    float* lp = dO + B;
-    float* D3 = lp + B;
-    float* D2 = D3 + B * kH;
-    float* D1 = D2 + B * kH;
-    float* part = D1 + B * kH;
-    hipLaunchKernelGGL(loss_kernel, dim3(g1d(B)), dim3(256), 0, st, O, y, B, q, dO, lp);
-    if (loss) hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, st, lp, B, loss);
-    // output layer (linear): gW4 = sum_b dO[b] A3[b, :], gb4 = sum_b dO[b]
-    wgrad(dO, A3, B, kH, 1, nullptr, nullptr, part, grad + kOffW4, grad + kOffB4, st);
-    hipLaunchKernelGGL(delta_kernel, dim3(g1d(B * kH)), dim3(256), 0, st, dO, w + kOffW4, A3, B,
-                       kH, 1, D3);
-    wgrad(D3, A2, B, kH, kH, nullptr, nullptr, part, grad + kOffW3, grad + kOffB3, st);
-    hipLaunchKernelGGL(delta_kernel, dim3(g1d(B * kH)), dim3(256), 0, st, D3, w + kOffW3, A2, B,
-                       kH, kH, D2);
-    wgrad(D2, A1, B, kH, kH, nullptr, nullptr, part, grad + kOffW2, grad + kOffB2, st);
-    hipLaunchKernelGGL(delta_kernel, dim3(g1d(B * kH)), dim3(256), 0, st, D2, w + kOffW2, A1, B,
-                       kH, kH, D1);
-    wgrad(D1, X, B, kIn, kH, mean, scale, part, grad + kOffW1, grad + kOffB1, st);
+    const int64_t t = (B + kMT - 1) / kMT;
+    hipLaunchKernelGGL(mlp_tile_kernel<false>, dim3((unsigned)(t < (1 << 20) ? t : (1 << 20))),
+                       dim3(kMW * 64), sizeof(MlpTile), st, X, nullptr, B, 0.f, w, mean, scale, out,
+                       nullptr, nullptr);
+    return hipGetLastError();
+}
+
+size_t mlp_grad_scratch_bytes(int64_t B) {
+    return (size_t)mlp_groups(B) * (kNParam * sizeof(float) + sizeof(double)) + 16;
+}
+
+// loss (device double, optional) and gradient of the mean pinball loss over the
+// batch; scratch: mlp_grad_scratch_bytes(B)
+hipError_t mlp_loss_grad(const float* w, const float* mean, const float* scale, const float* X,
+                         const float* y, int64_t B, float q, float* grad, void* scratch,
+                         double* loss, hipStream_t st) {
+    if (B == 0) return hipSuccess;
+    const unsigned groups = mlp_groups(B);
+    double* lpart = (double*)scratch;
+    float* part = (float*)(lpart + groups);
+    hipLaunchKernelGGL(mlp_tile_kernel<true>, dim3(groups), dim3(kMW * 64), sizeof(MlpTile), st, X,
+                       y, B, q, w, mean, scale, nullptr, part, lpart);
+    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((kNParam + 63) / 64)), dim3(256), 0, st,
+                       part, lpart, (int)groups, B, grad, loss);
     return hipGetLastError();
 }
 

@@ -407,3 +407,26 @@ def test_fused_inference_matches_oracle(H, orc, d, kernel, p0):
     assert np.all((tgt >= 1) & (tgt <= R))
     hm.close()
     mlp.close()
+
+
+@pytest.mark.parametrize("B", [63, 64, 65, 64 * 256, 64 * 256 + 1, 64 * 512 + 37])
+def test_tiles_match_oracle(H, orc, B):
+    """Batches at the edges of a 64-sample tile and of one tile per workgroup:
+    forward, loss and gradient against the oracle (the bounds of the tests
+    above)."""
+    w = synth.mlp_init_params(21)
+    w[-1] = 3.0
+    X, y = _features_data(B, 200 + B % 97)
+    mean = X.mean(axis=0).astype(np.float32)
+    sd = X.std(axis=0)
+    scale = np.where(sd > 1e-6, 1.0 / np.maximum(sd, 1e-30), 1.0).astype(np.float32)
+    mlp = H.RankMLP(w)
+    mlp.set_params(w, mean, scale)
+    out = mlp.forward(_dev(X)).cpu().numpy()
+    loss, g = mlp.loss_grad(_dev(X), _dev(y), q=0.9)
+    Xn = (X.astype(np.float64) - mean) * scale
+    assert _rel(out, orc.mlp_forward(w.astype(np.float64), Xn)) <= 1e-5
+    loss_o, g_o = orc.mlp_loss_grad(w.astype(np.float64), Xn, y.astype(np.float64), q=0.9)
+    assert abs(loss - loss_o) <= 1e-5 * abs(loss_o) + 1e-7
+    assert _rel(g.cpu().numpy().astype(np.float64), g_o) <= 1e-4
+    mlp.close()
