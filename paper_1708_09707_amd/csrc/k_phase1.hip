@@ -25,6 +25,8 @@
 //     coincident points) keep their V in the separate pool.
 #include "hmx_internal.h"
 
+#include <algorithm>
+
 namespace hmx {
 
 namespace {
@@ -66,33 +68,46 @@ struct P1Dec<uint16_t, float> {
 
 constexpr int kP1Threads = 256;
 constexpr int kP1Cols = 16;     // columns per lane group in flight
+constexpr int kP1BufWord3 = 0x00020000;  // 32-bit data format, the raw-buffer form on CDNA
+constexpr int kP1Nt = 2;        // non-temporal: every entry is read once per product
 constexpr int kP1Stage = 2048;  // rows of x a tile stages in LDS (taller tiles read x directly)
 
 // Tile pass.  meta[ms * t + 1] = first source column of tile t (tile t + 1's
 // entry ends it), meta[ms * t + 2] = data offset of the tile's matrix in
-// pool.  The tile's x rows are staged in LDS.  The workgroup's 256 threads
-// form groups of L lanes; a group takes kP1Cols consecutive columns at a
-// time, lane q covering 16-byte row vectors q, q + L, ... of each, and sums
-// each lane's products in registers; the kP1Cols sums are then reduced over
-// the group's lanes by a butterfly that halves the values per lane at each
-// of the first four exchanges (one shuffle per column instead of log2 L),
-// after which every lane holds the total of one column.  Narrow groups (16
-// lanes) give each lane several row vectors per column before the
-// reduction, so the exchanges are a small share of the work on tall tiles.
+// pool.  The tile's x rows are staged in LDS.  The waves form groups of L
+// lanes; a wave's groups take kP1Cols columns each at a time, the groups side
+// by side (load u of the wave covers consecutive columns, so whole cache lines
+// also where a column is no multiple of one), lane q covering 16-byte row
+// vectors q, q + L, ... of each, and sums each lane's products in registers;
+// the kP1Cols sums are then reduced over the group's lanes by a butterfly that
+// halves the values per lane at each of the first four exchanges (one shuffle
+// per column instead of log2 L), after which every lane holds the total of one
+// column.  Narrow groups (16 lanes) give each lane several row vectors per
+// column before the reduction, so the exchanges are a small share of the work
+// on tall tiles.  The columns of a tile are spread over gridDim.y workgroups
+// where the tiles alone leave the chip idle.  A column's sum does not depend on
+// either.  Bound by HBM.  Before, with 64-bit addresses per column, two waves a
+// SIMD and each group on 16 consecutive columns, and now: N = 100003 3-d FP32
+// (49-row tiles, 3.97 GB) 1124 and 883 us; N = 2^20 3-d BF16 symmetric (64-row
+// tiles, 14.9 GB) 3257 and 2543 us (5.9 TB/s); N = 2^14 3-d FP64 (256 tiles, 0.49
+// GB) 143 and 94 us; N = 4096 FP64 (64 tiles) 15 and 10 us; N = 2^19 2-d FP64
+// (6.0 GB) 1133-1176 and 1150-1188 us.
 template <typename S, typename T, int L>
-__global__ __launch_bounds__(kP1Threads) void p1_tile_kernel(
+__global__ __launch_bounds__(kP1Threads, 3) void p1_tile_kernel(
     int64_t ntiles, const int32_t* __restrict__ tile_lo, const int64_t* __restrict__ meta, int ms,
     int R, const S* __restrict__ pool, const T* __restrict__ vec, T* __restrict__ partial,
     int64_t pbase) {
     constexpr int VS = P1Dec<S, T>::n;
-    constexpr int G = kP1Threads / L;
+    constexpr int kWaves = kP1Threads / 64;
     static_assert(L >= 8 && L <= 64, "groups of 8, 16, 32 or 64 lanes");
     // halving exchanges (at most four: 16 values per lane down to one);
     // with 8 lanes three, and each lane keeps two column totals
     constexpr int HS = L >= 16 ? 4 : 3;
     constexpr int KEEP = kP1Cols >> HS;
     __shared__ T sx[kP1Stage];
-    const int g = threadIdx.x / L;
+    constexpr int SUB = 64 / L;  // groups of a wave
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int sub = (threadIdx.x & 63) / L;
     const int q = threadIdx.x % L;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int64_t c0 = meta[ms * t + 1];
@@ -105,27 +120,56 @@ __global__ __launch_bounds__(kP1Threads) void p1_tile_kernel(
         const S* __restrict__ base = pool + meta[ms * t + 2];
         // x of the tile (rows past it read as zero)
         const bool staged = ld <= kP1Stage;
+        // a batch's span past the descriptor's 31-bit offsets (leaves of
+        // millions of points): one column at a time, 64-bit addresses
+        const bool wide = (int64_t)SUB * kP1Cols * ld * (int64_t)sizeof(S) >= 0x7fffffff;
         if (staged) {
             for (int i = threadIdx.x; i < ld; i += kP1Threads) sx[i] = i < mt ? vec[r0 + i] : (T)0;
             __syncthreads();
         }
-        for (int cb = g * kP1Cols; cb < nc; cb += G * kP1Cols) {
+        for (int cb = ((int)blockIdx.y * kWaves + w) * SUB * kP1Cols; cb < nc;
+             cb += (int)gridDim.y * kWaves * SUB * kP1Cols) {
             T acc[kP1Cols];
 #pragma unroll
             for (int u = 0; u < kP1Cols; ++u) acc[u] = 0;
+            // one descriptor per batch and 32-bit offsets (a 64-bit address per
+            // column took the registers of half the waves)
+            const S* __restrict__ bp = base + (int64_t)cb * ld;
+            const auto rs =
+                __builtin_amdgcn_make_buffer_rsrc((void*)bp, 0, 0x7fffffff, kP1BufWord3);
+            const int last = nc - 1 - cb;
             for (int vi = q; vi < nvec; vi += L) {
                 u32x4 raw[kP1Cols];
+                const int row = vi * VS;
+                if (wide) {
+#pragma unroll 1
+                    for (int u = 0; u < kP1Cols; ++u) {
+                        const int cu = cb + u * SUB + sub;
+                        const S* p = base + (int64_t)(cu < nc ? cu : nc - 1) * ld + row;
+                        T a[VS];
+                        P1Dec<S, T>::get(*(const u32x4*)p, a);
+#pragma unroll
+                        for (int e = 0; e < VS; ++e)
+                            a[e] *= row + e < mt ? vec[r0 + row + e] : (T)0;
+                        T sum = a[0];
+#pragma unroll
+                        for (int e = 1; e < VS; ++e) sum += a[e];
+#pragma unroll
+                        for (int v = 0; v < kP1Cols; ++v) acc[v] += v == u ? sum : (T)0;
+                    }
+                    continue;
+                }
 #pragma unroll
                 for (int u = 0; u < kP1Cols; ++u) {
-                    const int c = cb + u < nc ? cb + u : nc - 1;  // past the end: never stored
-                    raw[u] = __builtin_nontemporal_load((const u32x4*)(base + (int64_t)c * ld) + vi);
+                    const int cu = u * SUB + sub;
+                    const int c = cu < last ? cu : last;  // past the end: never stored
+                    raw[u] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rs, (c * ld + row) * (int)sizeof(S), 0, kP1Nt);
                 }
                 T xv[VS];
 #pragma unroll
-                for (int e = 0; e < VS; ++e) {
-                    const int row = vi * VS + e;
-                    xv[e] = staged ? sx[row] : (row < mt ? vec[r0 + row] : (T)0);
-                }
+                for (int e = 0; e < VS; ++e)
+                    xv[e] = staged ? sx[row + e] : (row + e < mt ? vec[r0 + row + e] : (T)0);
 #pragma unroll
                 for (int u = 0; u < kP1Cols; ++u) {
                     T a[VS];
@@ -158,8 +202,10 @@ __global__ __launch_bounds__(kP1Threads) void p1_tile_kernel(
             }
             if ((q & (L >= 16 ? L / 16 - 1 : 0)) == 0) {
 #pragma unroll
-                for (int i = 0; i < KEEP; ++i)
-                    if (cb + off + i < nc) partial[pbase + c0 + cb + off + i] = acc[i];
+                for (int i = 0; i < KEEP; ++i) {
+                    const int c = cb + (off + i) * SUB + sub;
+                    if (c < nc) partial[pbase + c0 + c] = acc[i];
+                }
             }
         }
         if (staged) __syncthreads();  // sx is refilled by the next tile
@@ -426,9 +472,15 @@ hipError_t p1_tile_dispatch(int64_t ntiles, const int32_t* tile_lo, const int64_
     constexpr int VS = P1Dec<S, T>::n;
     const int need = (max_ld + VS - 1) / VS;  // row vectors of the tallest tile
     if (lanes == 0) lanes = need <= 8 ? 8 : (need <= 8 * 16 ? 16 : (need <= 8 * 32 ? 32 : 64));
-    const unsigned grid = (unsigned)(ntiles < (1 << 30) ? ntiles : (1 << 30));
+    const unsigned gx = (unsigned)(ntiles < (1 << 30) ? ntiles : (1 << 30));
+    // at least kP1Fill workgroups (eight a compute unit, two rounds of what is
+    // resident): fewer tiles split their columns.  64 tiles of an N = 4096 FP64
+    // product: 15 us unsplit, 10 split; at 2048 tiles and more no gain
+    constexpr int64_t kP1Fill = 2048;
+    const int64_t split = (kP1Fill + ntiles - 1) / ntiles;
+    const dim3 grid(gx, (unsigned)std::max<int64_t>(std::min<int64_t>(split, 16), 1));
 #define HMX_P1(LL)                                                                             \
-    hipLaunchKernelGGL((p1_tile_kernel<S, T, LL>), dim3(grid), dim3(kP1Threads), 0, st, ntiles, \
+    hipLaunchKernelGGL((p1_tile_kernel<S, T, LL>), grid, dim3(kP1Threads), 0, st, ntiles, \
                        tile_lo, meta, ms, R, (const S*)pool, (const T*)vec, (T*)partial, pbase)
     if (lanes == 8)
         HMX_P1(8);
