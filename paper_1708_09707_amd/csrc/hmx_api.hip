@@ -2450,6 +2450,26 @@ hmx_status cg_args(hmx_hmatrix_s* h, const void* b, const void* x, double rel_to
     return HMX_OK;
 }
 
+// one product; config: the row tiles' shape
+hmx_status matvec_call(hmx_hmatrix_s* h, const void* x, void* z, hmx_dtype vec_dtype,
+                       double alpha, double beta, void* stream, int config) {
+    const hmx_status cs = matvec_args(h, x, z, vec_dtype);
+    if (cs != HMX_OK) return cs;
+    hipEvent_t* ev = nullptr;
+    if (h->prof_calls < h->prof_max) ev = &h->prof_events[4 * h->prof_calls++];
+    if (h->far_np) {
+        const Allocator ua{h->prm.dev_alloc, h->prm.dev_free, h->prm.alloc_ctx};
+        AllocScope scope(&ua);
+        return guarded([&] { np_matvec(h, x, z, alpha, beta, (hipStream_t)stream, ev); });
+    }
+    const hipError_t e = matvec_launch(h, x, z, alpha, beta, (hipStream_t)stream, ev, config);
+    if (e != hipSuccess) {
+        set_err("matvec launch: %s", hipGetErrorString(e));
+        return HMX_ERR_DEVICE;
+    }
+    return HMX_OK;
+}
+
 // Textbook CG (Hestenes-Stiefel) from x = 0 on (H + sigma2 I); every buffer
 // of w is overwritten before it is read, so leftover contents do not matter.
 hmx_status cg_run(hmx_hmatrix_s* h, const void* b, void* x, double rel_tol, int32_t max_iter,
@@ -2479,8 +2499,9 @@ hmx_status cg_run(hmx_hmatrix_s* h, const void* b, void* x, double rel_tol, int3
     }
     res = 1.0;
     status = HMX_ERR_NOT_CONVERGED;
+    const int shape = h->rt_config < 0 ? kRowtileTall : h->rt_config;
     while (it < max_iter) {
-        hmx_status s = hmx_matvec(h, w.p, w.q, vdt, 1.0, 0.0, st);
+        hmx_status s = matvec_call(h, w.p, w.q, vdt, 1.0, 0.0, st, shape);
         if (s != HMX_OK) return s;
         check(launch_dot(w.p, w.q, n, f64, pa, sc + 1, st), "cg dot");
         check(launch_cg_update(x, w.r, w.p, w.q, sc, n, f64, pa, sc + 2, st), "cg update");
@@ -2504,7 +2525,7 @@ hmx_status cg_run(hmx_hmatrix_s* h, const void* b, void* x, double rel_tol, int3
     if (status != HMX_OK && it >= max_iter) set_err("CG did not converge in %d iterations", it);
     if (true_rel_res) {
         // r = b - (H + sigma2 I) x
-        hmx_status s = hmx_matvec(h, x, w.q, vdt, 1.0, 0.0, st);
+        hmx_status s = matvec_call(h, x, w.q, vdt, 1.0, 0.0, st, shape);
         if (s != HMX_OK) return s;
         check(launch_sub(w.r, b, w.q, n, f64, st), "cg residual");
         check(launch_dot(w.r, w.r, n, f64, pa, sc + 4, st), "cg residual");
@@ -2803,21 +2824,7 @@ hmx_status hmx_get_batch(hmx_hmatrix h, int32_t* nprob, int64_t* offsets) {
 
 hmx_status hmx_matvec(hmx_hmatrix h, const void* x, void* z, hmx_dtype vec_dtype, double alpha,
                       double beta, void* stream) {
-    const hmx_status cs = matvec_args(h, x, z, vec_dtype);
-    if (cs != HMX_OK) return cs;
-    hipEvent_t* ev = nullptr;
-    if (h->prof_calls < h->prof_max) ev = &h->prof_events[4 * h->prof_calls++];
-    if (h->far_np) {
-        const Allocator ua{h->prm.dev_alloc, h->prm.dev_free, h->prm.alloc_ctx};
-        AllocScope scope(&ua);
-        return guarded([&] { np_matvec(h, x, z, alpha, beta, (hipStream_t)stream, ev); });
-    }
-    const hipError_t e = matvec_launch(h, x, z, alpha, beta, (hipStream_t)stream, ev, h->rt_config);
-    if (e != hipSuccess) {
-        set_err("matvec launch: %s", hipGetErrorString(e));
-        return HMX_ERR_DEVICE;
-    }
-    return HMX_OK;
+    return matvec_call(h, x, z, vec_dtype, alpha, beta, stream, h ? h->rt_config : -1);
 }
 
 hmx_status hmx_matmat(hmx_hmatrix h, const void* X, int64_t ldx, void* Z, int64_t ldz,

@@ -522,6 +522,12 @@ hipError_t launch_int_stats(const int32_t* a, int64_t n, unsigned long long* out
 constexpr int kRowtileShapes = 6;
 constexpr int kRowtileConfigs = 3 * kRowtileShapes;
 constexpr unsigned kPersistentGrid = 2048;
+// config: -1 the shape by sizes; kRowtileTall: passes of 128 rows throughout.  The
+// shape sets the order of a row's sum, and CG at a small regularisation carries a
+// rounding of the product into the last digits a million times over, so the
+// solver's order stays that of one shape (FP64 N = 2^14 3-d, 64-row tiles: 225 us
+// against 234-238 us in narrower passes)
+constexpr int kRowtileTall = -2;
 // nmode 3: near field recomputed from soa (compute type, d x n) with kern
 hipError_t launch_rowtile(int64_t ntiles, const int32_t* tile_lo, const int64_t* meta,
                           const int64_t* widx, const void* upool, const void* npool,

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 CASES = [(60, 64, 2), (130, 64, 2), (1000, 1, 2), (1500, 7, 3), (3001, 17, 2), (4096, 64, 2),
-         (9000, 100, 3), (12000, 2500, 2), (20000, 9, 2), (33000, 32, 2)]
+         (9000, 100, 3), (12000, 2500, 2), (20000, 9, 2), (33000, 32, 2), (3000, 256, 2),
+         (16384, 128, 2), (70000, 100, 2), (150000, 256, 2)]
 
 
 @pytest.fixture(scope="module")
