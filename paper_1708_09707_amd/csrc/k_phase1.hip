@@ -214,7 +214,10 @@ __global__ __launch_bounds__(kP1Threads, 3) void p1_tile_kernel(
 
 // Column sums: target column k (t entry k of the vector pool) adds the
 // partials of its nt source pieces, rec[k] = {base (low, high), nt, l}:
-// partial[pfc[base + j] + l] for j = 0 .. nt - 1 in tile order.
+// partial[pfc[base + j] + l] for j = 0 .. nt - 1 in tile order.  Bound by the
+// latency of record, position, partial in turn: four pieces in flight (past the
+// last one: its address again, not added).  N = 2^20
+// 3-d BF16 465 us one by one, 378 now; N = 2^14 FP64 10.7 and 7.5 us.
 template <typename T>
 __global__ void p1_reduce_kernel(const int4* __restrict__ rec, int64_t ncols,
                                  const int64_t* __restrict__ pfc, const T* __restrict__ partial,
@@ -223,8 +226,18 @@ __global__ void p1_reduce_kernel(const int4* __restrict__ rec, int64_t ncols,
     if (k >= ncols) return;
     const int4 r = rec[k];
     const int64_t b = (int64_t)(((uint64_t)(uint32_t)r.y << 32) | (uint32_t)r.x);
+    constexpr int U = 4;
     T s = 0;
-    for (int j = 0; j < r.z; ++j) s += partial[pfc[b + j] + r.w];
+    for (int j = 0; j < r.z; j += U) {
+        int64_t at[U];
+        T v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) at[u] = pfc[b + (j + u < r.z ? j + u : r.z - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = partial[at[u] + r.w];
+#pragma unroll
+        for (int u = 0; u < U; ++u) s = j + u < r.z ? s + v[u] : s;
+    }
     vec[n + k] = s;
 }
 
