@@ -29,6 +29,8 @@
 // column c, in another order.
 #include "hmx_internal.h"
 
+#include <type_traits>
+
 namespace hmx {
 
 namespace {
@@ -462,143 +464,178 @@ struct MfUnit<uint16_t, 8> {
     }
 };
 
-// columns [ja, jb) of a staged chunk against their weights: column j's rows
-// for this lane start at base + j ld, its weights at sw[j M].  PB K-steps of
-// four columns are loaded (non-temporal: every entry is read once per
-// product) and only then used; past jb a load repeats column jb - 1 and its
-// weight is zero
-template <typename S, typename T, int M, int VR, int PB>
-__device__ __forceinline__ void mf_rows_part(const S* __restrict__ base, int ld, int ja, int jb,
-                                             const T* __restrict__ sw, int li, int lk,
-                                             typename MfmaOp<T>::Acc (&acc)[VR]) {
-    typedef MfUnit<S, VR> Un;
-    for (int j0 = ja; j0 < jb; j0 += 4 * PB) {
-        typename Un::Raw raw[PB];
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            const int j = j0 + 4 * b + lk;
-            raw[b] = __builtin_nontemporal_load(
-                (const typename Un::Raw*)(base + (int64_t)(j < jb ? j : jb - 1) * ld));
-        }
-        // all PB loads issued before the first use: keeps the scheduler from
-        // sinking them next to their instructions (two in flight otherwise)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            const int j = j0 + 4 * b + lk;
-            const bool live = j < jb && li < M;
-            const T wv = sw[(live ? j : ja) * M + (li < M ? li : 0)];
-            const T w = live ? wv : (T)0;
-            T a[VR];
-            Un::get(raw[b], a);
-#pragma unroll
-            for (int e = 0; e < VR; ++e) acc[e] = MfmaOp<T>::mac(a[e], w, acc[e]);
-        }
-    }
+constexpr int kMmSteps = 8;  // K-steps (of four columns) of a row-tile batch
+
+template <typename Raw>
+__device__ __forceinline__ Raw mm_buffer_load(__amdgpu_buffer_rsrc_t rs, int off) {
+    constexpr int kNt = 2;  // non-temporal: every entry is read once per product
+    if constexpr (sizeof(Raw) == 16)
+        return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kNt);
+    else
+        return __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, kNt);
 }
 
-// row tiles on the matrix cores: a workgroup of nw waves (blockDim.x / 64)
-// per (tile, group of nw slabs); wave w owns the 16 VR rows of its slab and
-// all M <= 16 right-hand sides.  The column weights pass through LDS, one
-// column per staging thread per chunk (KC columns, 16 KB of weights),
-// double-buffered: while a chunk is multiplied, the weights of the next one
-// are loaded into registers and the column indices of the one after are
-// read, so one barrier per chunk remains and no load waits on another.
-// Factor columns first, then the stored near field
-template <typename SU, typename SN, typename T, int M, int VR, int PB>
+// row tiles on the matrix cores: a workgroup per (tile, pass of NS slabs of 16 VR
+// rows); its KW waves take all M <= 16 right-hand sides of these rows and every
+// KW-th batch of B = 4 PB columns, factor columns first, then the stored near
+// field, and their sums meet in LDS at the end, in wave order.  Waves that split
+// the rows instead are a quarter of the workgroups, each four times as long, and
+// the last of them leave the chip idle; they also meet at every change of weights.
+// A wave's loads run one batch ahead: the registers of a K-step are loaded again
+// as soon as its instructions have read them, and with them its weights (a lane
+// keeps the index of one column of the next batch but one).  Columns past the
+// end read zero, outside their descriptor, and weigh zero.  The weights (128 bytes
+// a column in FP64) are the second largest traffic, 2 NS rows of matrix bytes to
+// each, and neighbouring tiles read the same ones: eighths of the tiles go
+// to one XCD each, which finds them in its own L2.
+// Bound by HBM and that gather.  N = 2^17 2-d FP64, 16 sides (9.2 GB): 2440 us
+// with waves by rows and weights through LDS, 2127 now (NS = 2, PB = 8; one slab
+// 2270, four 2460; without the order of tiles 2172).
+// WIDE: columns so tall that a batch passes a descriptor's 31-bit offsets
+// (millions of rows); 64-bit addresses, the last column repeated past the end.
+template <typename SU, typename SN, typename T, int M, int VR, int PB, int NS, bool WIDE>
 __global__ __launch_bounds__(256) void mm_rowtile_mfma_kernel(
     int64_t ntiles, const int32_t* __restrict__ tile_lo, const int64_t* __restrict__ meta,
     const int64_t* __restrict__ widx, const SU* __restrict__ upool, const SN* __restrict__ npool,
     const T* __restrict__ vec, const int32_t* __restrict__ perm, T alpha, T beta, T sigma2,
     T* __restrict__ Z, int64_t ldz, int R, int mr, int npass) {
     typedef MfmaOp<T> Op;
-    constexpr int RS = 16 * VR;              // rows of a wave's slab
-    constexpr int WV = 16 / (int)sizeof(T);  // weights per 16-byte move
-    static_assert(M % WV == 0, "whole 16-byte moves of weights");
-    typedef T WVec __attribute__((ext_vector_type(WV)));
-    constexpr int KCM = 16384 / (M * (int)sizeof(T));  // 16 KB of weights per buffer
-    __shared__ __align__(16) T sw[2][KCM * M];
-    const int nw = (int)(blockDim.x >> 6);
-    const int KC = min((int)blockDim.x, KCM);  // columns per chunk: one per staging thread
-    const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+    constexpr int B = 4 * PB;      // columns of a batch
+    constexpr int SR = 16 * VR;    // rows of a slab
+    constexpr int RS = SR * NS;    // rows of a wave
+    static_assert(B <= 64, "a lane per column of a batch");
+    constexpr int KW = 4;  // waves of a workgroup, each with every KW-th batch
+    __shared__ T part[(KW - 1) * NS * VR * 4 * 64];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63);
     const int li = lane & 15, lk = lane >> 4;
-    const int me = (int)threadIdx.x;
-    const bool stager = me < KC;
-    // one workgroup per (tile, group of nw slabs), the groups of a tile
-    // consecutive in the grid (workgroups running together read whole columns)
-    for (int64_t w = blockIdx.x; w < ntiles * npass; w += gridDim.x) {
+    const int lm = li < M ? li : 0;
+    const int64_t nwork = ntiles * npass, per = (nwork + 7) / 8;
+    for (int64_t v = blockIdx.x; v < per * 8; v += gridDim.x) {
+        const int64_t w = (v & 7) * per + (v >> 3);
+        if (w >= nwork) continue;
         const int64_t t = w / npass;
         const int32_t r0 = tile_lo[t];
         const int mt = tile_lo[t + 1] - r0;
         const int ld = mm_ld(mt, R);
-        const int slab0 = (int)(w - t * npass) * nw * RS;
-        if (slab0 >= ld) continue;  // the same for the whole workgroup
-        const int slab = slab0 + wv * RS;
-        const bool active = slab < ld;
-        // loads stay inside the column (a clamped lane's rows are past ld and discarded)
-        const int lrow = min(slab + li * VR, ld - VR);
+        const int slab = (int)(w - t * npass) * RS;
+        if (slab >= ld) continue;
         const int64_t k0 = meta[4 * t], k1 = meta[4 * t + 4];
         const int64_t ku = meta[4 * t + 5] - meta[4 * t + 1];
-        const SU* __restrict__ ubase = upool + meta[4 * t + 2] + lrow;
-        const SN* __restrict__ nbase = npool + meta[4 * t + 3] + lrow;
-        typename Op::Acc acc[VR];
+        typename Op::Acc acc[NS][VR];
 #pragma unroll
-        for (int e = 0; e < VR; ++e)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[e][v] = 0;
-        // this thread's column of chunk c is k0 + c KC + me
-        const int nch = (int)((k1 - k0 + KC - 1) / KC);
-        int64_t idx_next = stager && k0 + KC + me < k1 ? widx[k0 + KC + me] : 0;  // chunk 1
-        {
-            const bool own = stager && k0 + me < k1;
-            const int64_t i0 = own ? widx[k0 + me] : 0;
-            if (own)
-#pragma unroll
-                for (int c = 0; c < M; c += WV)
-                    *(WVec*)(&sw[0][me * M + c]) = *(const WVec*)(vec + i0 * M + c);
-        }
-        __syncthreads();
-        for (int ch = 0; ch < nch; ++ch) {
-            const int64_t kc = k0 + (int64_t)ch * KC;
-            const int nk = (int)min((int64_t)KC, k1 - kc);
-            // the next chunk's weights into registers, the indices of the one after
-            WVec wr[M / WV];
-            const bool has_next = stager && kc + KC + me < k1;
-            if (has_next)
-#pragma unroll
-                for (int c = 0; c < M / WV; ++c) wr[c] = *(const WVec*)(vec + idx_next * M + c * WV);
-            idx_next = stager && kc + 2 * KC + me < k1 ? widx[kc + 2 * KC + me] : 0;
-            if (active) {
-                const T* __restrict__ swc = sw[ch & 1];
-                const int ju = (int)max((int64_t)0, min((int64_t)nk, k0 + ku - kc));
-                if (ju > 0)
-                    mf_rows_part<SU, T, M, VR, PB>(ubase + (kc - k0) * ld, ld, 0, ju, swc, li, lk,
-                                                   acc);
-                if (ju < nk)
-                    mf_rows_part<SN, T, M, VR, PB>(nbase + (kc - k0 - ku) * ld, ld, ju, nk, swc,
-                                                   li, lk, acc);
-            }
-            if (has_next)
-#pragma unroll
-                for (int c = 0; c < M / WV; ++c) *(WVec*)(&sw[(ch + 1) & 1][me * M + c * WV]) = wr[c];
-            __syncthreads();
-        }
-        if (active && li < mr) {  // the group's real sides (mr <= M)
+        for (int s = 0; s < NS; ++s)
 #pragma unroll
             for (int e = 0; e < VR; ++e)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = slab + VR * Op::drow(lk, v) + e;
-                    if (row >= mt) continue;
-                    const int64_t gi = r0 + row;
-                    const int64_t zi = perm[gi] + li * ldz;
-                    T s = acc[e][v];
-                    if (sigma2 != (T)0) s += sigma2 * vec[gi * M + li];
-                    T out = alpha * s;
-                    if (beta != (T)0) out += beta * Z[zi];
-                    Z[zi] = out;
+                for (int r = 0; r < 4; ++r) acc[s][e][r] = 0;
+        auto pool = [&](const auto* base, const int64_t* wi, int64_t cols) {
+            typedef typename std::remove_const<
+                typename std::remove_reference<decltype(*base)>::type>::type S;
+            typedef MfUnit<S, VR> Un;
+            if (cols <= 0) return;
+            const int cb = ld * (int)sizeof(S);
+            unsigned off[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int row = slab + s * SR + li * VR;
+                off[s] = row < ld ? (unsigned)(lk * cb + row * (int)sizeof(S)) : 0x80000000u;
+            }
+            // columns of the batch from column c on
+            auto left = [&](int64_t c) {
+                return cols - c < B ? (int)(cols - c > 0 ? cols - c : 0) : B;
+            };
+            // slab s of K-step b (columns 4 b .. 4 b + 3) of that batch
+            auto fetch = [&](int64_t c, int b, int s) {
+                if constexpr (WIDE) {
+                    const int64_t j = c + 4 * b + lk;
+                    const int row = min(slab + s * SR + li * VR, ld - VR);
+                    return *(const typename Un::Raw*)(base + (j < cols ? j : cols - 1) * ld + row);
                 }
+                const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(base + c * ld), 0,
+                                                                  left(c) * cb, 0x00020000);
+                return mm_buffer_load<typename Un::Raw>(rs, (int)(off[s] + (unsigned)(4 * b * cb)));
+            };
+            // a lane's column index of the batch from c on, and K-step b's weight
+            // out of the batch's indices
+            auto index = [&](int64_t c) { return wi[c + lane < cols ? c + lane : cols - 1]; };
+            auto weight = [&](int64_t idx, int b) {
+                const int64_t i = __shfl(idx, 4 * b + lk, 64);
+                return vec[i * M + lm];
+            };
+            typename Un::Raw raw[NS][PB];
+            T wt[PB];
+            int64_t idx = index(wv * B), idxn = index((wv + KW) * B);
+#pragma unroll
+            for (int b = 0; b < PB; ++b) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s) raw[s][b] = fetch(wv * B, b, s);
+                wt[b] = weight(idx, b);
+            }
+            // (nothing pending at the loop's head, or the compiler waits for every
+            // load there in each iteration)
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            for (int64_t c = wv * B; c < cols; c += KW * B) {
+                const int64_t in = idxn;
+                idxn = index(c + 2 * KW * B);
+                const int n = left(c);
+#pragma unroll
+                for (int b = 0; b < PB; ++b) {
+                    const T wb = 4 * b + lk < n ? wt[b] : (T)0;
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        T a[VR];
+                        Un::get(raw[s][b], a);
+#pragma unroll
+                        for (int e = 0; e < VR; ++e) acc[s][e] = Op::mac(a[e], wb, acc[s][e]);
+                    }
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) raw[s][b] = fetch(c + KW * B, b, s);
+                    wt[b] = weight(in, b);
+                    if (b % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        };
+        pool(upool + meta[4 * t + 2], widx + k0, ku);
+        pool(npool + meta[4 * t + 3], widx + k0 + ku, k1 - k0 - ku);
+        if (wv > 0)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int e = 0; e < VR; ++e)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        part[(((wv - 1) * NS + s) * VR * 4 + e * 4 + r) * 64 + lane] = acc[s][e][r];
+        __syncthreads();
+        if (wv == 0)
+#pragma unroll
+            for (int k = 0; k < KW - 1; ++k)
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int e = 0; e < VR; ++e)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            acc[s][e][r] += part[((k * NS + s) * VR * 4 + e * 4 + r) * 64 + lane];
+        if (wv == 0 && li < mr) {  // the group's real sides (mr <= M)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int e = 0; e < VR; ++e)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = slab + s * SR + VR * Op::drow(lk, r) + e;
+                        if (row >= mt) continue;
+                        const int64_t gi = r0 + row;
+                        const int64_t zi = perm[gi] + li * ldz;
+                        T sum = acc[s][e][r];
+                        if (sigma2 != (T)0) sum += sigma2 * vec[gi * M + li];
+                        T out = alpha * sum;
+                        if (beta != (T)0) out += beta * Z[zi];
+                        Z[zi] = out;
+                    }
         }
+        __syncthreads();  // part is refilled by the next tile
     }
 }
 
@@ -606,7 +643,9 @@ __global__ __launch_bounds__(256) void mm_rowtile_mfma_kernel(
 // the tile's rows.  A wave takes 16 source columns (lane i's column cb + i)
 // and runs down all rows, 4 VR per K-step; the tile's X rows are staged in
 // LDS transposed (side-major, row stride XT), so a lane's VR rows of one side
-// are one contiguous read; wider tiles read X from the vector itself
+// are one contiguous read; wider tiles read X from the vector itself.  The
+// columns of few tiles are spread over gridDim.y workgroups.  N = 2^17 2-d
+// FP64 (512 tiles, 1.2 GB): 403 us with one workgroup a tile, 357 split.
 template <typename S, typename T, int M, int VR>
 __global__ __launch_bounds__(256) void mm_p1_mfma_kernel(int64_t ntiles,
                                                          const int32_t* __restrict__ tile_lo,
@@ -643,7 +682,7 @@ __global__ __launch_bounds__(256) void mm_p1_mfma_kernel(int64_t ntiles,
             }
             __syncthreads();
         }
-        for (int cb = wv * 16; cb < nc; cb += nw * 16) {
+        for (int cb = ((int)blockIdx.y * nw + wv) * 16; cb < nc; cb += (int)gridDim.y * nw * 16) {
             // columns past nc repeat the last one; their sums are not stored
             const S* __restrict__ cp = base + (int64_t)min(cb + li, nc - 1) * ld;
             typename Op::Acc acc;
@@ -738,14 +777,17 @@ hipError_t launch_mm_p1(int M, int64_t ntiles, const int32_t* tile_lo, const int
     if (ntiles == 0) return hipSuccess;
     if (M == 8 || M == 16) {
         // matrix cores; R (entries per 16 bytes) is a multiple of the load's rows
-        const unsigned g = (unsigned)std::min<int64_t>(ntiles, 1 << 20);
+        // eight workgroups a compute unit, by splitting the columns of few tiles
+        const int64_t fill = (2048 + ntiles - 1) / ntiles;
+        const dim3 g((unsigned)std::min<int64_t>(ntiles, 1 << 20),
+                     (unsigned)std::max<int64_t>(std::min<int64_t>(fill, 16), 1));
 #define HMX_P1M(S, T, VR)                                                                       \
     if (M == 8)                                                                                 \
-        hipLaunchKernelGGL((mm_p1_mfma_kernel<S, T, 8, VR>), dim3(g), dim3(256), 0, st, ntiles,  \
+        hipLaunchKernelGGL((mm_p1_mfma_kernel<S, T, 8, VR>), g, dim3(256), 0, st, ntiles,  \
                            tile_lo, meta, ms, R, (const S*)pool, (const T*)vec, (T*)partial,     \
                            pbase);                                                              \
     else                                                                                        \
-        hipLaunchKernelGGL((mm_p1_mfma_kernel<S, T, 16, VR>), dim3(g), dim3(256), 0, st, ntiles, \
+        hipLaunchKernelGGL((mm_p1_mfma_kernel<S, T, 16, VR>), g, dim3(256), 0, st, ntiles, \
                            tile_lo, meta, ms, R, (const S*)pool, (const T*)vec, (T*)partial,     \
                            pbase)
         if (smode == 0) {
@@ -788,13 +830,6 @@ hipError_t launch_mm_p1_reduce(int M, const int4* rec, int64_t ncols, const int6
     return hipGetLastError();
 }
 
-#ifndef HMX_MM_PB
-#define HMX_MM_PB 16
-#endif
-#ifndef HMX_MM_BF16_VR
-#define HMX_MM_BF16_VR 8
-#endif
-
 hipError_t launch_mm_rowtile(int M, int64_t ntiles, const int32_t* tile_lo, const int64_t* meta,
                              const int64_t* widx, const void* upool, const void* npool,
                              const void* vec, const int32_t* perm, double alpha, double beta,
@@ -804,36 +839,48 @@ hipError_t launch_mm_rowtile(int M, int64_t ntiles, const int32_t* tile_lo, cons
     if (ntiles == 0) return hipSuccess;
     if (mr < 1 || mr > M) return hipErrorInvalidValue;
     if ((M == 8 || M == 16) && nmode != 3) {
-        // matrix cores: a wave per slab of 16 VR rows, up to four slabs per workgroup
-        const int vr = fmode == 0 ? 2 : (fmode == 2 && nmode == 2 ? HMX_MM_BF16_VR : 4);
+        // matrix cores: passes of two slabs of 16 VR rows, or one where that holds
+        // the tile
+        const int vr = fmode == 0 ? 2 : (fmode == 2 && nmode == 2 ? 8 : 4);
         if (R % vr) return hipErrorInvalidValue;
-        const int ldmax = mm_ld(max_tile, R), rs = 16 * vr;
-        const int nw = std::max(1, std::min(4, (ldmax + rs - 1) / rs));
-        const int passes = (ldmax + nw * rs - 1) / (nw * rs);
-        const dim3 grid((unsigned)std::min<int64_t>(ntiles * passes, 1 << 20));
-#define HMX_RTM(SU, SN, T, VR)                                                                   \
-    if (M == 8)                                                                                  \
-        hipLaunchKernelGGL((mm_rowtile_mfma_kernel<SU, SN, T, 8, VR, HMX_MM_PB>), grid, dim3(64 * nw), 0, st, \
-                           ntiles, tile_lo, meta, widx, (const SU*)upool, (const SN*)npool,      \
-                           (const T*)vec, perm, (T)alpha, (T)beta, (T)sigma2, (T*)Z, ldz, R, mr, \
-                           passes);                                                              \
+        const int ldmax = mm_ld(max_tile, R), slabs = (ldmax + 16 * vr - 1) / (16 * vr);
+        const int es = fmode == 0 ? 8 : (fmode == 2 && nmode == 2 ? 2 : 4);
+        const bool wide = (int64_t)4 * kMmSteps * es * ldmax >= 0x7fffffff;
+        const int ns = slabs > 1 && !wide ? 2 : 1;
+        const int passes = (slabs + ns - 1) / ns;
+        const dim3 grid((unsigned)std::min<int64_t>((ntiles * passes + 7) / 8 * 8, 1 << 20));
+#define HMX_RTW(SU, SN, T, VR, MM, NS, WW)                                                       \
+    hipLaunchKernelGGL((mm_rowtile_mfma_kernel<SU, SN, T, MM, VR, kMmSteps, NS, WW>), grid,      \
+                       dim3(256), 0, st, ntiles, tile_lo, meta, widx, (const SU*)upool,          \
+                       (const SN*)npool, (const T*)vec, perm, (T)alpha, (T)beta, (T)sigma2,      \
+                       (T*)Z, ldz, R, mr, passes)
+#define HMX_RTN(SU, SN, T, VR, MM)                                                               \
+    if (wide)                                                                                    \
+        HMX_RTW(SU, SN, T, VR, MM, 1, true);                                                     \
+    else if (ns == 1)                                                                            \
+        HMX_RTW(SU, SN, T, VR, MM, 1, false);                                                    \
     else                                                                                         \
-        hipLaunchKernelGGL((mm_rowtile_mfma_kernel<SU, SN, T, 16, VR, HMX_MM_PB>), grid, dim3(64 * nw), 0,   \
-                           st, ntiles, tile_lo, meta, widx, (const SU*)upool, (const SN*)npool,  \
-                           (const T*)vec, perm, (T)alpha, (T)beta, (T)sigma2, (T*)Z, ldz, R, mr, \
-                           passes)
+        HMX_RTW(SU, SN, T, VR, MM, 2, false)
+#define HMX_RTM(SU, SN, T, VR)                                                                   \
+    if (M == 8) {                                                                                \
+        HMX_RTN(SU, SN, T, VR, 8);                                                               \
+    } else {                                                                                     \
+        HMX_RTN(SU, SN, T, VR, 16);                                                              \
+    }
         if (fmode == 0 && nmode == 0) {
             HMX_RTM(double, double, double, 2);
         } else if (fmode == 1 && nmode == 1) {
             HMX_RTM(float, float, float, 4);
         } else if (fmode == 2 && nmode == 2) {
-            HMX_RTM(uint16_t, uint16_t, float, HMX_MM_BF16_VR);
+            HMX_RTM(uint16_t, uint16_t, float, 8);
         } else if (fmode == 2 && nmode == 1) {
             HMX_RTM(uint16_t, float, float, 4);
         } else {
             return hipErrorInvalidValue;
         }
 #undef HMX_RTM
+#undef HMX_RTN
+#undef HMX_RTW
         return hipGetLastError();
     }
     if (mr != M) return hipErrorInvalidValue;  // the vector-unit forms take whole groups

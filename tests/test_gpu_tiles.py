@@ -46,3 +46,26 @@ def test_product_over_tiles(H, orc, n, leaf, d, dtype, symmetric):
     print("  error %.2e" % err, flush=True)
     assert err <= tol
     hm.close()
+
+
+def test_matmat_columns_past_31_bits(H):
+    """Sixteen sides on one tile of 8.4 million rows: a batch of its columns passes
+    the 31-bit offsets of a buffer descriptor (a near-field block; the ACA takes no
+    blocks so tall).  Every column equals the product with one vector to
+    rounding: a row sums 40 terms, 1e-13 of it."""
+    n1, n2, m = 8400000, 40, 16
+    print("one dense block %d x %d, FP64, %d sides" % (n1, n2, m), flush=True)
+    p1 = torch.from_numpy(synth.uniform_points(n1, 2, 7)).to("cuda:0")
+    p2 = torch.from_numpy(synth.uniform_points(n2, 2, 8)).to("cuda:0")
+    hm = H.HMatrix.rect(p1, p2, "gaussian", 4.0, compute_dtype="f64", leaf_size=1 << 24, eta=1.5)
+    assert hm.stats().n_adm == 0 and hm.stats().n_dense == 1
+    X = torch.from_numpy(synth.normal_vector(m * n2, 9).reshape(m, n2)).to("cuda:0")
+    Z = torch.empty((m, n1), dtype=torch.float64, device="cuda:0")
+    H.hmx_matmat(hm.h, X, Z)
+    worst = 0.0
+    for c in range(m):
+        z = hm.matvec(X[c].contiguous())
+        worst = max(worst, float(torch.linalg.norm(Z[c] - z) / torch.linalg.norm(z)))
+    print("  worst column vs matvec: %.2e" % worst, flush=True)
+    assert worst <= 1e-13
+    hm.close()
