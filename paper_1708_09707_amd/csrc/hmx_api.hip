@@ -1733,8 +1733,8 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
         check(launch_piece_data(h->pieces.as<Piece>(), h->npieces, h->tile_lo.as<int32_t>(),
                                 h->adm.as<int4>(), h->dense.as<int4>(), rfo.as<int64_t>(), F.p,
                                 f64 ? h->soa64.p : h->soa32.p, n, d,
-                                kernel_fn(h->kern, h->kd), h->upool.p, nullptr, smode, h->nmode, 1,
-                                st),
+                                kernel_fn(h->kern, h->kd), h->upool.p, nullptr, smode, h->nmode, false,
+                                h->upool_entries, st),
               "piece data (factors)");
         h->Ru = R;
         // ---- phase-1 sources (t = V^T x by row tiles) ----
@@ -1794,8 +1794,8 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
                   "V tile meta");
             alloc(h->vtpool, (size_t)std::max<int64_t>(h->vtpool_entries, 1) * ssz, "V pool");
             check(launch_vpiece_data(h->vpieces.as<Piece>(), nv, h->tile_lo.as<int32_t>(),
-                                     h->adm.as<int4>(), vfo.as<int64_t>(), F.p, h->Rv,
-                                     h->vtpool.p, smode, st),
+                                     h->adm.as<int4>(), vfo.as<int64_t>(), F.p, h->vtpool.p,
+                                     smode, h->vtpool_entries, st),
                   "V pool");
             check(launch_pfc(h->vpieces.as<Piece>(), vv.as<uint32_t>(), vcl.as<int64_t>(), nv, nv,
                              vbase, h->pfc.as<int64_t>() + pfc_u, st),
@@ -1835,7 +1835,7 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
                                     h->adm.as<int4>(), h->dense.as<int4>(), nullptr, nullptr,
                                     f64 ? h->soa64.p : h->soa32.p, n, d,
                                     kernel_fn(h->kern, h->kd), h->upool.p, h->npool.p, smode,
-                                    h->nmode, 2, st),
+                                    h->nmode, true, h->npool_entries, st),
                   "piece data (near field)");
         check(hipStreamSynchronize(st), "near-field sync");
     }

@@ -489,8 +489,11 @@ hipError_t launch_piece_data(const Piece* pieces, int64_t np, const int32_t* til
                              const void* Usrc /* storage type */, const void* soa, int64_t n,
                              int d, KernelFn kern,
                              void* upool, void* npool, int fmode, int nmode,
-                             int which /*0 all, 1 factor pieces, 2 near-field pieces*/,
-                             hipStream_t st);
+                             bool near /*the near-field pieces, else the factors'*/,
+                             int64_t entries /*of the pool(s) filled*/, hipStream_t st);
+// workgroups of the sums over all leaves: one atomic per wave on one word, so the
+// waves are bounded (894342 leaves: 328 us with a thread per leaf, now 28)
+constexpr int kStatBlocks = 256;
 // smode: storage mode 0 = F64, 1 = F32, 2 = BF16 storage with F32 arithmetic
 hipError_t launch_compact_v(const int4* blocks, int64_t nblocks, const int32_t* rank,
                             const int64_t* cap_voff, int64_t cap_base, const int64_t* voff,
@@ -636,8 +639,8 @@ hipError_t launch_vpiece_sizes(const Piece* src, const uint32_t* order, int64_t 
                                hipStream_t st);
 hipError_t launch_vpiece_layout(Piece* pieces, int64_t np, const int64_t* doff, hipStream_t st);
 hipError_t launch_vpiece_data(const Piece* pieces, int64_t np, const int32_t* tile_lo,
-                              const int4* adm, const int64_t* vfo, const void* src, int R,
-                              void* pool, int smode, hipStream_t st);
+                              const int4* adm, const int64_t* vfo, const void* src, void* pool,
+                              int smode, int64_t entries, hipStream_t st);
 
 // batched build assembly (k_batch.hip)
 hipError_t launch_add_i32(int32_t* dst, const int32_t* src, int64_t cnt, int32_t c,

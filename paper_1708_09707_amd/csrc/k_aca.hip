@@ -51,6 +51,8 @@
 
 #include "hmx_internal.h"
 
+#include <algorithm>
+
 namespace hmx {
 
 namespace {
@@ -1765,14 +1767,14 @@ namespace {
 __global__ void aca_work_kernel(const int4* __restrict__ blocks, const int32_t* __restrict__ rank,
                                 const int32_t* __restrict__ steps, int64_t nb,
                                 unsigned long long* __restrict__ out) {
-    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     unsigned long long ev = 0, fl = 0;
-    if (b < nb) {
+    for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < nb;
+         b += (int64_t)gridDim.x * blockDim.x) {
         const int4 bl = blocks[b];
         const unsigned long long m = bl.y - bl.x, nc = bl.w - bl.z;
         const unsigned long long r = rank[b] > 0 ? rank[b] : 0, s = steps[b] > 0 ? steps[b] : 0;
-        ev = s * m + r * nc;
-        fl = r > 0 ? 2ull * r * (r - 1) * (m + nc) : 0;
+        ev += s * m + r * nc;
+        fl += r > 0 ? 2ull * r * (r - 1) * (m + nc) : 0;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -1790,8 +1792,8 @@ hipError_t launch_aca_work(const int4* blocks, const int32_t* rank, const int32_
                            int64_t nb, unsigned long long* out, hipStream_t st) {
     hipError_t e = hipMemsetAsync(out, 0, 2 * sizeof(unsigned long long), st);
     if (e != hipSuccess || nb == 0) return e;
-    hipLaunchKernelGGL(aca_work_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st,
-                       blocks, rank, steps, nb, out);
+    const unsigned grid = (unsigned)std::min<int64_t>((nb + 255) / 256, kStatBlocks);
+    hipLaunchKernelGGL(aca_work_kernel, dim3(grid), dim3(256), 0, st, blocks, rank, steps, nb, out);
     return hipGetLastError();
 }
 

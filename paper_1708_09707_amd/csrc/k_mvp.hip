@@ -273,6 +273,33 @@ __device__ __forceinline__ void store_unit(S* __restrict__ dst, const S (&v)[R])
     for (int q = 0; q < kVec; ++q) out[q] = w[q];
 }
 
+// columns c = c0, c0 + per, ... < nc of R rows: src + c sld (any alignment) to
+// dst + c dld; rows from `rows` on are zero.  Whole units load 16 bytes at a
+// time, four columns in flight
+template <typename S, int R>
+__device__ __forceinline__ void copy_columns(const S* __restrict__ src, int64_t sld,
+                                             S* __restrict__ dst, int dld, int c0, int per, int nc,
+                                             int rows) {
+    constexpr int U = 4;
+    for (int c = c0; c < nc; c += U * per) {
+        S v[U][R];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int cu = c + u * per < nc ? c + u * per : c;
+            const S* __restrict__ sp = src + (int64_t)cu * sld;
+            if (rows >= R) {
+                __builtin_memcpy(v[u], sp, sizeof(v[u]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < R; ++e) v[u][e] = e < rows ? sp[e] : (S)0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c + u * per < nc) store_unit<S, R>(dst + (int64_t)(c + u * per) * dld, v[u]);
+    }
+}
+
 // R values of T, converted to S, stored as one unit
 template <typename S, typename T, int R>
 struct UnitStore {
@@ -357,45 +384,48 @@ __device__ __forceinline__ void near_dispatch(const KernelEval<T>& K, const T* _
     }
 }
 
-// One workgroup per piece.  Each thread owns a group of R consecutive rows
-// of the tile (their coordinates stay in registers) and sweeps a set of the
-// piece's columns, writing R entries per column with 16-byte stores; rows
-// past the tile's end are zero.  A factor piece copies rows row0 .. of its U
-// columns, a near-field piece evaluates phi.
-template <typename SU, typename SN, typename T, int R>
+// TPP threads (a wave or a workgroup) per piece.  Each thread owns a group of R
+// consecutive rows of the tile (their coordinates stay in registers) and sweeps
+// a set of the piece's columns, writing R entries per column with 16-byte
+// stores; rows past the tile's end are zero.  A factor piece copies rows row0 ..
+// of its U columns (NEAR false), a near-field piece evaluates phi (true; one
+// kernel for both holds the registers of either).  Small pieces are bound by the
+// latency of piece, block, offset and entry in turn, so by the pieces in flight.
+// N = 200003 3-d BF16 (49-row tiles, 2.9 GB of near field, 1.8 GB each of U and V):
+// U 3.0 ms as a workgroup per piece and two bytes a load, now 1.25; near field
+// 3.25, now 1.57; V (vpiece_data_kernel) 2.4, now 1.5.  N = 2^20 2-d FP32
+// (256-row tiles): U 2.9 and 2.8 ms, V 3.6 and 2.8, near field 7.1 ms as before.
+template <typename SU, typename SN, typename T, int R, int TPP, bool NEAR>
 __global__ __launch_bounds__(256) void piece_data_kernel(
     const Piece* __restrict__ pieces, int64_t np, const int32_t* __restrict__ tile_lo,
     const int4* __restrict__ adm, const int4* __restrict__ dense,
     const int64_t* __restrict__ uoff, const SU* __restrict__ Usrc, const T* __restrict__ soa,
-    int64_t n, int d, KernelEval<T> K, SU* __restrict__ upool, SN* __restrict__ npool,
-    int which) {
-    const int tid = threadIdx.x;
-    for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {
+    int64_t n, int d, KernelEval<T> K, SU* __restrict__ upool, SN* __restrict__ npool) {
+    constexpr int PPB = 256 / TPP;  // pieces per workgroup
+    const int tid = threadIdx.x % TPP;
+    // the same for a whole wave, so the piece's fields are scalars
+    const int sub = TPP == 256 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / TPP);
+    for (int64_t p = blockIdx.x * (int64_t)PPB + sub; p < np;
+         p += (int64_t)gridDim.x * PPB) {
         const Piece pc = pieces[p];
-        if (is_recompute<SN>::value && pc.blk < 0) continue;  // near field evaluated per product
-        if ((which == 1 && pc.blk < 0) || (which == 2 && pc.blk >= 0)) continue;
+        if ((pc.blk < 0) != NEAR) continue;
         const int32_t r0 = tile_lo[pc.tile];
         const int mt = tile_lo[pc.tile + 1] - r0;
         const int ld = tile_ld(mt, R);
         const int upc = ld / R;  // row groups per column
-        const bool is_factor = pc.blk >= 0;
-        const int4 bl = is_factor ? adm[pc.blk] : dense[-pc.blk - 1];
+        const int4 bl = NEAR ? dense[-pc.blk - 1] : adm[pc.blk];
         const int m = bl.y - bl.x;
         // thread -> row group g and columns cstart, cstart + per, ...
-        const int per = upc <= 256 ? 256 / upc : 1;
-        for (int gs = 0; gs < upc; gs += 256) {
-            const int g = upc <= 256 ? tid % upc : gs + tid;
-            const int cstart = upc <= 256 ? tid / upc : 0;
-            if (upc <= 256 ? tid >= per * upc : g >= upc) continue;
+        const int per = upc <= TPP ? TPP / upc : 1;
+        for (int gs = 0; gs < upc; gs += TPP) {
+            const int g = upc <= TPP ? tid % upc : gs + tid;
+            const int cstart = upc <= TPP ? tid / upc : 0;
+            if (upc <= TPP ? tid >= per * upc : g >= upc) continue;
             const int i0 = g * R;
-            if (is_factor) {
+            if constexpr (!NEAR) {
                 const SU* __restrict__ src = Usrc + uoff[pc.blk] + pc.row0 + i0;
-                for (int c = cstart; c < pc.ncols; c += per) {
-                    SU v[R];
-#pragma unroll
-                    for (int e = 0; e < R; ++e) v[e] = i0 + e < mt ? src[(int64_t)c * m + e] : (SU)0;
-                    store_unit<SU, R>(upool + pc.d_off + (int64_t)c * ld + i0, v);
-                }
+                copy_columns<SU, R>(src, m, upool + pc.d_off + i0, ld, cstart, per, pc.ncols,
+                                    mt - i0);
             } else if constexpr (!is_recompute<SN>::value) {
                 T x[R][3];
 #pragma unroll
@@ -411,6 +441,35 @@ __global__ __launch_bounds__(256) void piece_data_kernel(
     }
 }
 
+// The V pool's pieces: rows row0 .. of the piece's V columns, TPP threads a piece
+template <typename S, int TPP>
+__global__ __launch_bounds__(256) void vpiece_data_kernel(const Piece* __restrict__ pieces,
+                                                          int64_t np,
+                                                          const int32_t* __restrict__ tile_lo,
+                                                          const int4* __restrict__ adm,
+                                                          const int64_t* __restrict__ vfo,
+                                                          const S* __restrict__ src,
+                                                          S* __restrict__ pool) {
+    constexpr int PPB = 256 / TPP, R = 16 / (int)sizeof(S);
+    const int tid = threadIdx.x % TPP;
+    // the same for a whole wave, so the piece's fields are scalars
+    const int sub = TPP == 256 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / TPP);
+    for (int64_t p = blockIdx.x * (int64_t)PPB + sub; p < np;
+         p += (int64_t)gridDim.x * PPB) {
+        const Piece pc = pieces[p];
+        const int mt = tile_lo[pc.tile + 1] - tile_lo[pc.tile];
+        const int ld = tile_ld(mt, R);
+        const int upc = ld / R;
+        const int4 bl = adm[pc.blk];
+        const S* __restrict__ s = src + vfo[pc.blk] + pc.row0;
+        const int per = upc <= TPP ? TPP / upc : 1;
+        if (upc <= TPP && tid >= per * upc) continue;
+        for (int g = upc <= TPP ? tid % upc : tid; g < upc; g += upc <= TPP ? upc : TPP)
+            copy_columns<S, R>(s + g * R, bl.w - bl.z, pool + pc.d_off + g * R, ld,
+                               upc <= TPP ? tid / upc : 0, per, pc.ncols, mt - g * R);
+    }
+}
+
 template <typename T>
 __global__ void gather_x_kernel(const T* __restrict__ x, const int32_t* __restrict__ perm,
                                 int64_t n, T* __restrict__ xm, int64_t base) {
@@ -421,10 +480,13 @@ __global__ void gather_x_kernel(const T* __restrict__ x, const int32_t* __restri
 // out[0] = max, out[1] = sum of n int32 values (integer atomics: order-free)
 __global__ void int_stats_kernel(const int32_t* __restrict__ a, int64_t n,
                                  unsigned long long* __restrict__ out) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    int32_t v = i < n ? a[i] : 0;
-    int32_t mx = v;
-    int64_t sm = v;
+    int32_t mx = 0;
+    int64_t sm = 0;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        mx = a[i] > mx ? a[i] : mx;
+        sm += a[i];
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const int32_t u = __shfl_xor(mx, o, 64);
@@ -512,6 +574,7 @@ __global__ void chunk_bounds_kernel(const int64_t* __restrict__ cap_off, int64_t
 // partial row sets are summed in LDS in a fixed order and the tile is
 // scattered to the original order.
 constexpr int kTileThreads = 256;
+constexpr int kWaveUnits = 512;
 constexpr int kChunk = 2048;
 constexpr int kUnroll = 16;
 constexpr int kEvalUnroll = 4;  // near-field columns evaluated per iteration (recompute mode)
@@ -959,16 +1022,33 @@ int rows_per_unit(int fmode, int nmode) {
 hipError_t launch_piece_data(const Piece* pieces, int64_t np, const int32_t* tile_lo,
                              const int4* adm, const int4* dense, const int64_t* uoff,
                              const void* Usrc, const void* soa, int64_t n, int d, KernelFn kern,
-                             void* upool, void* npool, int fmode, int nmode, int which,
-                             hipStream_t st) {
-    if (np == 0) return hipSuccess;
-    const unsigned grid = grid_cap(np, 1 << 20);
+                             void* upool, void* npool, int fmode, int nmode, bool near,
+                             int64_t entries, hipStream_t st) {
+    if (np == 0 || (near && nmode == 3)) return hipSuccess;
+    // a wave per piece up to kWaveUnits 16-byte units a piece on average: with 49-row
+    // BF16 tiles (some 60 and 340 units, factor and near-field) 1.25 against 3.0 ms
+    // and 1.57 against 3.25; a near-field piece of 256 x 256 FP32 has 16384
+    // units, which a wave would take one after another
+    const bool wave = entries / np <= (int64_t)kWaveUnits * rows_per_unit(fmode, nmode);
+    const unsigned grid = grid_cap(wave ? (np + 3) / 4 : np, 1 << 20);
 // each combination's unit (rows_per_unit) is a template argument
 #define HMX_PD(SU, SN, T, R)                                                                  \
     if (R != rows_per_unit(fmode, nmode)) return hipErrorInvalidValue;                        \
-    else hipLaunchKernelGGL((piece_data_kernel<SU, SN, T, R>), dim3(grid), dim3(256), 0, st,     \
-                       pieces, np, tile_lo, adm, dense, uoff, (const SU*)Usrc, (const T*)soa, \
-                       n, d, KernelEval<T>(kern), (SU*)upool, (SN*)npool, which)
+    else if (near) {                                                                          \
+        HMX_PK(SU, SN, T, R, true);                                                           \
+    } else {                                                                                  \
+        HMX_PK(SU, SN, T, R, false);                                                          \
+    }
+#define HMX_PK(SU, SN, T, R, NEAR)                                                            \
+    if (wave)                                                                                 \
+        hipLaunchKernelGGL((piece_data_kernel<SU, SN, T, R, 64, NEAR>), dim3(grid), dim3(256), \
+                           0, st, pieces, np, tile_lo, adm, dense, uoff, (const SU*)Usrc,     \
+                           (const T*)soa, n, d, KernelEval<T>(kern), (SU*)upool, (SN*)npool); \
+    else                                                                                      \
+        hipLaunchKernelGGL((piece_data_kernel<SU, SN, T, R, 256, NEAR>), dim3(grid),          \
+                           dim3(256), 0, st, pieces, np, tile_lo, adm, dense, uoff,           \
+                           (const SU*)Usrc, (const T*)soa, n, d, KernelEval<T>(kern),         \
+                           (SU*)upool, (SN*)npool)
     if (fmode == 0 && nmode == 0) {
         HMX_PD(double, double, double, 2);
     } else if (fmode == 1 && nmode == 1) {
@@ -987,6 +1067,31 @@ hipError_t launch_piece_data(const Piece* pieces, int64_t np, const int32_t* til
         return hipErrorInvalidValue;
     }
 #undef HMX_PD
+#undef HMX_PK
+    return hipGetLastError();
+}
+
+hipError_t launch_vpiece_data(const Piece* pieces, int64_t np, const int32_t* tile_lo,
+                              const int4* adm, const int64_t* vfo, const void* src, void* pool,
+                              int smode, int64_t entries, hipStream_t st) {
+    if (np == 0) return hipSuccess;
+    const bool wave = entries / np <= (int64_t)kWaveUnits * rows_per_unit(smode, smode);
+    const unsigned grid = grid_cap(wave ? (np + 3) / 4 : np, 1 << 20);
+#define HMX_VP(S)                                                                             \
+    if (wave)                                                                                 \
+        hipLaunchKernelGGL((vpiece_data_kernel<S, 64>), dim3(grid), dim3(256), 0, st, pieces,  \
+                           np, tile_lo, adm, vfo, (const S*)src, (S*)pool);                   \
+    else                                                                                      \
+        hipLaunchKernelGGL((vpiece_data_kernel<S, 256>), dim3(grid), dim3(256), 0, st, pieces, \
+                           np, tile_lo, adm, vfo, (const S*)src, (S*)pool)
+    if (smode == 0) {
+        HMX_VP(double);
+    } else if (smode == 1) {
+        HMX_VP(float);
+    } else {
+        HMX_VP(uint16_t);
+    }
+#undef HMX_VP
     return hipGetLastError();
 }
 
@@ -1053,8 +1158,8 @@ hipError_t launch_int_stats(const int32_t* a, int64_t n, unsigned long long* out
                             hipStream_t st) {
     hipError_t e = hipMemsetAsync(out, 0, 2 * sizeof(unsigned long long), st);
     if (e != hipSuccess || n == 0) return e;
-    hipLaunchKernelGGL(int_stats_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a,
-                       n, out);
+    hipLaunchKernelGGL(int_stats_kernel, dim3(grid_cap((n + 255) / 256, kStatBlocks)), dim3(256), 0,
+                       st, a, n, out);
     return hipGetLastError();
 }
 

@@ -443,33 +443,6 @@ __global__ void vpiece_layout_kernel(Piece* __restrict__ pieces, int64_t np,
     if (i < np) pieces[i].d_off = doff[i];
 }
 
-// copy the V rows of the V pieces (source: column-major V_b at vfo[b] in the
-// exact pool, |sigma_b| rows), zero padding rows; one workgroup per piece
-template <typename S>
-__global__ __launch_bounds__(256) void vpiece_data_kernel(const Piece* __restrict__ pieces,
-                                                          int64_t np,
-                                                          const int32_t* __restrict__ tile_lo,
-                                                          const int4* __restrict__ adm,
-                                                          const int64_t* __restrict__ vfo,
-                                                          const S* __restrict__ src, int R,
-                                                          S* __restrict__ pool) {
-    for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {
-        const Piece pc = pieces[p];
-        const int mt = tile_lo[pc.tile + 1] - tile_lo[pc.tile];
-        const int ld = p1_ld(mt, R);
-        const int4 bl = adm[pc.blk];
-        const int64_t len = bl.w - bl.z;
-        const S* __restrict__ s = src + vfo[pc.blk] + pc.row0;
-        S* __restrict__ d = pool + pc.d_off;
-        const int tot = ld * pc.ncols;  // one piece: at most ld x 128 entries
-        for (int e = threadIdx.x; e < tot; e += blockDim.x) {
-            const int c = e / ld;
-            const int i = e - c * ld;
-            d[e] = i < mt ? s[(int64_t)c * len + i] : (S)0;
-        }
-    }
-}
-
 unsigned g1(int64_t n, int bs = 256) {
     const int64_t b = (n + bs - 1) / bs;
     return (unsigned)(b < (1 << 30) ? b : (1 << 30));
@@ -635,23 +608,6 @@ hipError_t launch_vpiece_sizes(const Piece* src, const uint32_t* order, int64_t 
 hipError_t launch_vpiece_layout(Piece* pieces, int64_t np, const int64_t* doff, hipStream_t st) {
     if (np == 0) return hipSuccess;
     hipLaunchKernelGGL(vpiece_layout_kernel, dim3(g1(np)), dim3(256), 0, st, pieces, np, doff);
-    return hipGetLastError();
-}
-
-hipError_t launch_vpiece_data(const Piece* pieces, int64_t np, const int32_t* tile_lo,
-                              const int4* adm, const int64_t* vfo, const void* src, int R,
-                              void* pool, int smode, hipStream_t st) {
-    if (np == 0) return hipSuccess;
-    const unsigned grid = (unsigned)(np < (1 << 20) ? np : (1 << 20));
-    if (smode == 0)
-        hipLaunchKernelGGL(vpiece_data_kernel<double>, dim3(grid), dim3(256), 0, st, pieces, np,
-                           tile_lo, adm, vfo, (const double*)src, R, (double*)pool);
-    else if (smode == 1)
-        hipLaunchKernelGGL(vpiece_data_kernel<float>, dim3(grid), dim3(256), 0, st, pieces, np,
-                           tile_lo, adm, vfo, (const float*)src, R, (float*)pool);
-    else
-        hipLaunchKernelGGL(vpiece_data_kernel<uint16_t>, dim3(grid), dim3(256), 0, st, pieces, np,
-                           tile_lo, adm, vfo, (const uint16_t*)src, R, (uint16_t*)pool);
     return hipGetLastError();
 }
 
