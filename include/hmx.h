@@ -420,11 +420,13 @@ hmx_status hmx_graph_destroy(hmx_graph g);
  * launch.  Host-blocking. */
 hmx_status hmx_autotune(hmx_hmatrix h, int32_t reps, void* stream, int32_t* choice,
                         double* times_ms);
-/* Select a row-tile configuration directly (-1: the default, one workgroup
- * per row pass of 128 rows (configuration 10, 11 or 12: 16, 32 or 64 lanes
+/* Select a row-tile configuration directly (-1: the default, one workgroup per
+ * row pass, whose lanes follow from the tiles' heights and number; CG's products
+ * then keep passes of 128 rows (configuration 10, 11 or 12: 16, 32 or 64 lanes
  * per row group for 8, 4 or 2 rows per 16-byte vector), narrower when the
- * handle's largest tile is shorter; and the default phase-1 lanes too, so a
- * handle returns to its untuned products). */
+ * handle's largest tile is shorter, so that its iterates do not depend on the
+ * choice; and the default phase-1 lanes too, so a handle returns to its untuned
+ * products). */
 hmx_status hmx_set_tile_config(hmx_hmatrix h, int32_t config);
 
 /* Conjugate gradients for (H + sigma2 I) c = b, the kernel ridge regression

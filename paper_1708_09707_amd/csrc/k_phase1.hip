@@ -7,8 +7,8 @@
 // phase 2: its rows are the points of sigma_b, so the part of V_b inside one
 // row tile (leaf cluster) T is a "source piece", stored with the tile's
 // other source pieces as one contiguous column-major ld_T x C matrix.  One
-// workgroup per tile streams that matrix once and forms, for every column,
-// the partial inner product with x|T; a second pass sums each column's
+// workgroup per tile (several where tiles are few) streams that matrix once and
+// forms, for every column, the partial inner product with x|T; a second pass sums each column's
 // partials over the tiles of sigma_b in tile order (a fixed order, so the
 // product is deterministic).
 //
