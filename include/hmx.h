@@ -176,8 +176,8 @@ typedef struct {
                                 reads every stored factor twice (as a leaf's
                                 U and as its mirror's V) */
     /* Optional device allocator (both NULL: the library's own, which keeps
-     * released blocks in a process-wide cache for later builds; hmx_trim
-     * empties it).  When dev_alloc is set, every device buffer of this build
+     * released blocks in a process-wide cache for later builds, as long as
+     * 4 GiB of the device stay free beside them; hmx_trim empties it).  When dev_alloc is set, every device buffer of this build
      * and of the handle's later calls (hmx_autotune's scratch vectors,
      * hmx_cg_solve's work vectors) is obtained as dev_alloc(bytes, alloc_ctx)
      * (bytes a multiple of 256; the memory must be device memory of the
@@ -263,8 +263,8 @@ typedef struct {
                                   driver instead of the library's block cache
                                   (memory the process released before is
                                   cleared by the driver on allocation) */
-    int64_t alloc_flushes;    /* cache flushes during the build (an allocation
-                                 failed and every cached block was freed) */
+    int64_t alloc_flushes;    /* times during the build that cached blocks went
+                                 back to the driver for lack of free memory */
 } hmx_stats;
 
 /* Fill *p with the defaults: leaf 256, eta 1.5, eps 1e-5, aca_eta 0,

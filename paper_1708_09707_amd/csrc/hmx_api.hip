@@ -3,20 +3,18 @@
 // sizes buffers, launches, and reads back the few counters that size the
 // next step (one per block-tree level, as in Algorithm 4, and one per pool).
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <map>
 #include <memory>
 #include <mutex>
 #include <new>
 #include <string>
-#include <unordered_set>
 #include <vector>
 
+#include "block_cache.h"
 #include "hmx_internal.h"
 
 using namespace hmx;
@@ -38,87 +36,38 @@ struct Fail {
     hmx_status s;
 };
 
-// Process-wide cache of device blocks.  Builds allocate and release the same
-// large pools again and again (capacity scratch, factor and near-field
-// pools); returning them to the driver and mapping them anew each time costs
-// seconds on a busy device, so released blocks are kept per device and
-// reused best-fit (a block is reused for requests of 3/4 of its size or
-// more).  A failed device allocation flushes the cache and retries once.
-// Blocks enter the cache only after the work using them has completed (the
-// build synchronises its stream before releasing scratch, destroy
-// synchronises the device).
-struct DeviceCache {
-    std::mutex mu;
-    std::multimap<size_t, std::pair<int, void*>> blocks;  // size -> (device, ptr)
-    size_t cached = 0;
-    // every block this library obtained with hipMalloc and has not freed:
-    // only these may enter the cache and be freed by it
-    std::unordered_set<void*> owned;
+// the calls behind the process-wide cache of device blocks
+struct HipDriver {
+    int device() {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        return dev;
+    }
+    bool alloc(void** p, size_t bytes, bool* oom) {
+        const hipError_t e = hipMalloc(p, bytes);
+        *oom = e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation;
+        if (e == hipSuccess) return true;
+        (void)hipGetLastError();
+        set_err("%s", hipGetErrorString(e));
+        return false;
+    }
+    bool free(void* p) {
+        if (hipFree(p) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
+    void sync() { (void)hipDeviceSynchronize(); }
+    bool free_bytes(size_t* fr) {
+        size_t tot = 0;
+        if (hipMemGetInfo(fr, &tot) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
 };
+using DeviceCache = BlockCache<HipDriver>;
 DeviceCache& cache() {
     static DeviceCache* c = new DeviceCache();  // never destroyed: process lifetime
     return *c;
-}
-
-// bytes the library obtained from the driver (cache misses) and cache
-// flushes, over the process: a handle's stats report their growth during
-// its build
-std::atomic<int64_t> g_fresh_bytes{0}, g_flushes{0};
-
-size_t cache_round(size_t bytes) {
-    const size_t g = bytes >= ((size_t)64 << 20) ? ((size_t)2 << 20) : 256;
-    return (bytes + g - 1) / g * g;
-}
-
-// *bytes: requested size in, size of the block handed out on return
-hipError_t cache_alloc(void** p, size_t* bytes) {
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    DeviceCache& c = cache();
-    {
-        std::lock_guard<std::mutex> lk(c.mu);
-        for (auto it = c.blocks.lower_bound(*bytes); it != c.blocks.end(); ++it) {
-            if (it->first / 4 * 3 > *bytes) break;
-            if (it->second.first != dev) continue;
-            *p = it->second.second;
-            *bytes = it->first;
-            c.cached -= it->first;
-            c.blocks.erase(it);
-            return hipSuccess;
-        }
-    }
-    hipError_t e = hipMalloc(p, *bytes);
-    if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-        (void)hipGetLastError();
-        std::lock_guard<std::mutex> lk(c.mu);
-        (void)hipDeviceSynchronize();
-        for (auto& b : c.blocks) {
-            c.owned.erase(b.second.second);
-            (void)hipFree(b.second.second);
-        }
-        c.blocks.clear();
-        c.cached = 0;
-        g_flushes.fetch_add(1);
-        e = hipMalloc(p, *bytes);
-    }
-    if (e == hipSuccess) {
-        std::lock_guard<std::mutex> lk(c.mu);
-        c.owned.insert(*p);
-        g_fresh_bytes.fetch_add((int64_t)*bytes);
-    }
-    return e;
-}
-
-// a block back into the cache; a pointer the library did not allocate is
-// never cached (so the cache never frees memory another allocator owns)
-void cache_free(void* p, size_t bytes) {
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    DeviceCache& c = cache();
-    std::lock_guard<std::mutex> lk(c.mu);
-    if (c.owned.count(p) == 0) return;
-    c.blocks.insert({bytes, {dev, p}});
-    c.cached += bytes;
 }
 
 // A caller's device allocator (hmx_params.dev_alloc / dev_free / alloc_ctx).
@@ -157,7 +106,7 @@ struct DevBuf {
             if (from.alloc)
                 from.free(p, bytes, from.ctx);
             else
-                cache_free(p, bytes);
+                cache().free(p, bytes);
         }
         p = nullptr;
         bytes = 0;
@@ -247,14 +196,13 @@ void alloc(DevBuf& b, size_t bytes, const char* what) {
         b.from = *g_user_alloc;
         return;
     }
-    bytes = cache_round(bytes);
-    hipError_t e = cache_alloc(&b.p, &bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
+    bytes = DeviceCache::round(bytes);
+    bool oom = false;
+    if (!cache().alloc(&b.p, &bytes, &oom)) {
         (void)hipDeviceSynchronize();  // in-flight work may still use released blocks
         b.p = nullptr;
-        set_err("device allocation of %zu bytes for %s failed: %s", bytes, what,
-                hipGetErrorString(e));
+        const std::string why = g_err;  // (the driver's)
+        set_err("device allocation of %zu bytes for %s failed: %s", bytes, what, why.c_str());
         throw Fail{HMX_ERR_OOM};
     }
     b.bytes = bytes;
@@ -403,7 +351,7 @@ struct hmx_hmatrix_s {
     int far_np = 0;  // factors recomputed by every matvec
     NpPlan np;
     // the process-wide allocation counters when the handle was created
-    int64_t fresh0 = g_fresh_bytes.load(), flush0 = g_flushes.load();
+    int64_t fresh0 = cache().fresh_bytes(), flush0 = cache().flushes();
     // rectangular A(Y1 x Y2): the union holds Y1 (rows, [0, nrows)) then Y2
     // (columns, [col0, col0 + ncols)); the row tiles are Y1's leaf clusters,
     // the first ntiles_rows tiles.  Square handles: rows = columns = [0, n).
@@ -460,8 +408,8 @@ void finish_stats(hmx_hmatrix_s* h, std::chrono::steady_clock::time_point t_all)
     S.tile_config = h->rt_config;
     S.rows = h->nrows;
     S.cols = h->ncols;
-    S.alloc_fresh_bytes = g_fresh_bytes.load() - h->fresh0;
-    S.alloc_flushes = g_flushes.load() - h->flush0;
+    S.alloc_fresh_bytes = cache().fresh_bytes() - h->fresh0;
+    S.alloc_flushes = cache().flushes() - h->flush0;
     S.phase_ms[7] = ms_since(t_all);
     // algorithmic bytes of one matvec with beta = 0: the near field once,
     // U_b and V_b of every admissible leaf once (with the symmetric far
@@ -1041,12 +989,8 @@ int64_t aca_budget(const hmx_hmatrix_s* h) {
     if (h->prm.aca_chunk_mb <= 0) {
         size_t fr = 0, tot = 0;
         check(hipMemGetInfo(&fr, &tot), "memory info");
-        size_t cached = 0;
-        {
-            std::lock_guard<std::mutex> lk(cache().mu);
-            cached = cache().cached;
-        }
-        budget_bytes = std::max<int64_t>((int64_t)((fr + cached) / 10 * 4), (int64_t)1 << 30);
+        budget_bytes =
+            std::max<int64_t>((int64_t)((fr + cache().cached()) / 10 * 4), (int64_t)1 << 30);
     }
     return std::max<int64_t>(budget_bytes / (int64_t)h->esz, 1);
 }
@@ -1721,12 +1665,7 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
         if (keep && !aca_keep.from.alloc) {
             size_t fr = 0, tot = 0;
             check(hipMemGetInfo(&fr, &tot), "memory info");
-            size_t cached = 0;
-            {
-                std::lock_guard<std::mutex> lk(cache().mu);
-                cached = cache().cached;
-            }
-            keep = fr + cached >= ubytes + ((size_t)4 << 30);
+            keep = fr + cache().cached() >= ubytes + DeviceCache::kReserve;
         }
         if (!keep) aca_keep.release();
         alloc(h->upool, ubytes, "factor pool");
@@ -3684,17 +3623,7 @@ hmx_status hmx_destroy(hmx_hmatrix h) {
 }
 
 hmx_status hmx_trim(int64_t* released_bytes) {
-    DeviceCache& c = cache();
-    std::lock_guard<std::mutex> lk(c.mu);
-    (void)hipDeviceSynchronize();
-    int64_t tot = 0;
-    for (auto& b : c.blocks) {
-        c.owned.erase(b.second.second);
-        (void)hipFree(b.second.second);
-        tot += (int64_t)b.first;
-    }
-    c.blocks.clear();
-    c.cached = 0;
+    const int64_t tot = cache().trim();
     if (released_bytes) *released_bytes = tot;
     return HMX_OK;
 }

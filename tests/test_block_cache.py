@@ -1,0 +1,196 @@
+"""The cache of device blocks against a driver of a stated size, on the CPU: kept
+blocks never take the memory that the runtime and other allocators need,
+blocks are reused, and every block goes back where it came from."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <string>
+#include <vector>
+#include "block_cache.h"
+
+static const size_t GB = (size_t)1 << 30, MB = (size_t)1 << 20;
+
+struct Card {                       // two devices of 288 GB
+    size_t free_[2] = {288 * GB, 288 * GB};
+    int dev = 0;
+    std::map<void*, std::pair<int, size_t>> held;
+    uintptr_t next = 4096;
+    int mallocs = 0;
+};
+struct Fake {
+    Card* c = nullptr;
+    int device() { return c->dev; }
+    bool alloc(void** p, size_t bytes, bool* oom) {
+        *oom = bytes > c->free_[c->dev];
+        if (*oom) return false;
+        c->free_[c->dev] -= bytes;
+        *p = (void*)(c->next += 4096);
+        c->held[*p] = {c->dev, bytes};
+        ++c->mallocs;
+        return true;
+    }
+    bool free(void* p) {
+        auto it = c->held.find(p);
+        if (it == c->held.end()) { printf("freed a block that is not held\n"); exit(1); }
+        c->free_[it->second.first] += it->second.second;
+        c->held.erase(it);
+        return true;
+    }
+    void sync() {}
+    bool free_bytes(size_t* f) { *f = c->free_[c->dev]; return true; }
+};
+using Cache = hmx::BlockCache<Fake>;
+
+#define EXPECT(x) do { if (!(x)) { printf("%s:%d: %s\n", name, __LINE__, #x); return 1; } } while (0)
+
+struct Block { void* p; size_t n; };
+static Block take(Cache& c, size_t n, bool* ok = nullptr) {
+    Block b{nullptr, Cache::round(n)};
+    bool oom, got = c.alloc(&b.p, &b.n, &oom);
+    if (ok) *ok = got;
+    return b;
+}
+
+// whenever blocks are kept, the reserve is free
+static bool reserved(Card& k, Cache& c) { return c.cached() == 0 || k.free_[k.dev] >= Cache::kReserve; }
+
+// three FP64 handles of 45 GB, each build with a scratch of 60 GB, released, then
+// builds of other sizes; a private segment of 0.4 GB has to fit after each step
+static int sequence(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    std::vector<Block> live;
+    for (int i = 0; i < 3; ++i) {
+        Block s = take(c, 60 * GB), a = take(c, 30 * GB), b = take(c, 15 * GB);
+        EXPECT(reserved(k, c));
+        c.free(s.p, s.n);
+        EXPECT(reserved(k, c));
+        live.push_back(a);
+        live.push_back(b);
+    }
+    for (auto& b : live) { c.free(b.p, b.n); EXPECT(reserved(k, c)); }
+    live.clear();
+    unsigned r = 12345;
+    for (int i = 0; i < 20000; ++i) {
+        r = r * 1664525u + 1013904223u;
+        const size_t n = (size_t)((r >> 8) % 40000 + 1) * (i % 3 ? MB : MB / 1024);
+        if (live.size() > 12 || (r >> 5) % 2) {
+            if (!live.empty()) {
+                const size_t q = (r >> 9) % live.size();
+                c.free(live[q].p, live[q].n);
+                live.erase(live.begin() + q);
+            }
+        } else {
+            bool ok;
+            Block b = take(c, n, &ok);
+            EXPECT(ok);
+            EXPECT(b.n >= n && b.n / 4 * 3 <= Cache::round(n));
+            live.push_back(b);
+        }
+        // (blocks under kLarge come back without a look: MBs, of which few)
+        EXPECT(c.cached() == 0 || k.free_[0] + 64 * MB >= Cache::kReserve);
+    }
+    return 0;
+}
+
+// a block of the same size is reused; a second build of the same sizes maps nothing
+static int reuse(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    for (int i = 0; i < 4; ++i) {
+        Block s = take(c, 60 * GB), a = take(c, 45 * GB), t = take(c, 1000);
+        if (i) EXPECT(k.mallocs == 3);
+        c.free(s.p, s.n); c.free(a.p, a.n); c.free(t.p, t.n);
+    }
+    EXPECT(c.fresh_bytes() == (int64_t)(105 * GB + 1024) && c.flushes() == 0);
+    return 0;
+}
+
+// another allocator of the process takes memory: the next large block that comes
+// back makes room, and what is missing comes from the smallest block that covers it
+static int others(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    Block a = take(c, 100 * GB), b = take(c, 10 * GB), d = take(c, 20 * GB);
+    c.free(a.p, a.n);
+    c.free(b.p, b.n);
+    k.free_[0] -= 155 * GB;  // 3 GB left
+    c.free(d.p, d.n);
+    EXPECT(k.free_[0] == 13 * GB && c.cached() == 120 * GB);
+    return 0;
+}
+
+// a request beyond the card fails, with everything idle given back and live blocks kept
+static int too_large(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    Block a = take(c, 100 * GB), b = take(c, 50 * GB);
+    c.free(b.p, b.n);
+    bool ok;
+    take(c, 200 * GB, &ok);
+    EXPECT(!ok && c.cached() == 0 && k.held.size() == 1 && k.held.count(a.p));
+    take(c, 188 * GB, &ok);  // all that is left: live data may use the reserve
+    EXPECT(ok);
+    return 0;
+}
+
+// blocks of another device are neither handed out nor given back for this one
+static int devices(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    k.dev = 1;
+    Block a = take(c, 100 * GB);
+    c.free(a.p, a.n);
+    k.dev = 0;
+    Block b = take(c, 100 * GB), d = take(c, 186 * GB);
+    EXPECT(b.p != a.p && k.held.count(a.p) && c.cached() == 100 * GB);
+    c.free(d.p, d.n);  // 2 GB were left: goes back at once
+    EXPECT(k.held.count(a.p) && k.held.size() == 2 && c.cached() == 100 * GB);
+    EXPECT(c.trim() == (int64_t)(100 * GB) && k.held.size() == 1 && k.held.count(b.p));
+    return 0;
+}
+
+// a pointer of another allocator never enters
+static int foreign(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    int x;
+    c.free(&x, GB);
+    EXPECT(c.cached() == 0);
+    return 0;
+}
+
+int main(int argc, char** argv) {
+    const std::string n = argv[1];
+    if (n == "sequence") return sequence(argv[1]);
+    if (n == "reuse") return reuse(argv[1]);
+    if (n == "others") return others(argv[1]);
+    if (n == "too_large") return too_large(argv[1]);
+    if (n == "devices") return devices(argv[1]);
+    if (n == "foreign") return foreign(argv[1]);
+    return 2;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("block_cache")
+    (d / "t.cpp").write_text(PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-pthread", "-I",
+                           os.path.join(ROOT, "paper_1708_09707_amd", "csrc"), str(d / "t.cpp"),
+                           "-o", str(d / "t")])
+    return str(d / "t")
+
+
+@pytest.mark.parametrize("case", ["sequence", "reuse", "others", "too_large", "devices", "foreign"])
+def test_block_cache(program, case):
+    r = subprocess.run([program, case], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
