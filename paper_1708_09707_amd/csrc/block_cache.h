@@ -183,4 +183,22 @@ class BlockCache {
     int64_t fresh_ = 0, flushes_ = 0;
 };
 
+// b grown to at least `bytes` (the block handed out may be larger than asked, so
+// each buffer is held to its own size): grow(b, bytes) replaces it
+template <typename Buf, typename Grow>
+void fit(Buf& b, size_t bytes, Grow&& grow) {
+    if (!b.p || b.bytes < bytes) grow(b, bytes);
+}
+
+// keys and work space of a sort that is repeated with other counts
+template <typename Buf>
+struct SortSpace {
+    Buf keys, scratch;
+    template <typename Grow>
+    void reserve(size_t keys_bytes, size_t scratch_bytes, Grow&& grow) {
+        fit(keys, keys_bytes, grow);
+        fit(scratch, scratch_bytes, grow);
+    }
+};
+
 }  // namespace hmx

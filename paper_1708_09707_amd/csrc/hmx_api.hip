@@ -208,6 +208,20 @@ void alloc(DevBuf& b, size_t bytes, const char* what) {
     b.bytes = bytes;
 }
 
+// grow a work buffer without keeping its contents (the stream is synchronised
+// first: the old block may still be in use by queued work)
+void ensure(DevBuf& b, size_t bytes, hipStream_t st, const char* what) {
+    if (b.p && b.bytes >= bytes) return;
+    if (b.p) check(hipStreamSynchronize(st), "work buffer sync");
+    alloc(b, bytes, what);
+}
+
+// (a scratch that is too small is an error here, not a write past its end)
+hipError_t sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int bits, const DevBuf& scratch,
+                      hipStream_t st) {
+    return radix_sort_pairs(keys, vals, n, bits, scratch.p, scratch.bytes, st);
+}
+
 template <typename T>
 T read_scalar(const T* dev, hipStream_t st) {
     T v;
@@ -601,8 +615,8 @@ void stage_partition(hmx_hmatrix_s* h, const void* pts, int pts_f64, hipStream_t
         DevBuf scratch;
         alloc(scratch, radix_sort_scratch_bytes(n), "sort scratch");
         const int bits = d == 3 ? 63 : 64;
-        check(radix_sort_pairs(h->codes.as<uint64_t>(), h->perm.as<uint32_t>(), n, bits,
-                               scratch.p, st),
+        check(sort_pairs(h->codes.as<uint64_t>(), h->perm.as<uint32_t>(), n, bits,
+                               scratch, st),
               "radix sort");
         alloc(h->soa64, (size_t)n * d * 8, "coords f64");
         if (!f64) alloc(h->soa32, (size_t)n * d * 4, "coords f32");
@@ -929,7 +943,7 @@ void interleave(const int4* blocks, const int32_t* levels, int64_t nb, const int
     int bits = 8;
     while ((1ll << (bits - 8)) < nsl) ++bits;
     alloc(sscr, radix_sort_scratch_bytes(nb), "interleave sort");
-    check(radix_sort_pairs(keys.as<uint64_t>(), o.perm.as<uint32_t>(), nb, bits, sscr.p, st),
+    check(sort_pairs(keys.as<uint64_t>(), o.perm.as<uint32_t>(), nb, bits, sscr, st),
           "interleave sort");
     keys.release();
     sscr.release();
@@ -964,20 +978,15 @@ AcaArgs aca_args_base(const hmx_hmatrix_s* h, const AcaPlan& plan) {
 
 // The blocks of a level-sorted chunk grouped by size class (stable): order
 // (nb entries) and the classes' bounds (kAcaClasses + 1 device entries)
-struct ClassSort {
-    DevBuf keys, scratch;
-};
+using ClassSort = SortSpace<DevBuf>;
 
 void class_order(ClassSort& cs, const int4* blocks, const int32_t* levels, int64_t nb, int lvl0,
                  uint32_t* order, int64_t* bounds, hipStream_t st) {
-    if (!cs.keys.p || cs.keys.bytes < (size_t)nb * 8) {
-        if (cs.keys.p) check(hipStreamSynchronize(st), "class sort");
-        alloc(cs.keys, (size_t)nb * 8, "class keys");
-        alloc(cs.scratch, radix_sort_scratch_bytes(nb), "class sort");
-    }
+    cs.reserve((size_t)nb * 8, radix_sort_scratch_bytes(nb),
+               [&](DevBuf& b, size_t bytes) { ensure(b, bytes, st, "class sort"); });
     check(launch_class_keys(blocks, levels, nb, lvl0, cs.keys.as<uint64_t>(), order, st),
           "class keys");
-    check(radix_sort_pairs(cs.keys.as<uint64_t>(), order, nb, 8, cs.scratch.p, st), "class sort");
+    check(sort_pairs(cs.keys.as<uint64_t>(), order, nb, 8, cs.scratch, st), "class sort");
     check(launch_class_bounds(cs.keys.as<uint64_t>(), nb, bounds, st), "class bounds");
 }
 
@@ -1116,7 +1125,7 @@ void np_plan(hmx_hmatrix_s* h, const AcaPlan& plan, const int4* Lb, const int32_
                                vals.as<uint32_t>(), pcs.as<int2>(), st),
           "piece fill");
     alloc(sscr, radix_sort_scratch_bytes(npcs), "piece sort");
-    check(radix_sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), npcs, tbits + cbits, sscr.p,
+    check(sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), npcs, tbits + cbits, sscr,
                            st),
           "piece sort");
     sscr.release();
@@ -1213,7 +1222,7 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
             int bits = 32;
             while (bits < 64 && (1ll << (bits - 32)) <= n) ++bits;
             alloc(sscr, radix_sort_scratch_bytes(na), "mirror sort");
-            check(radix_sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), na, bits, sscr.p, st),
+            check(sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), na, bits, sscr, st),
                   "mirror sort");
             check(launch_mirror_find(h->adm.as<int4>(), na, keys.as<uint64_t>(),
                                      vals.as<uint32_t>(), h->partner.as<int32_t>(), bad.as<int>(),
@@ -1618,7 +1627,7 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
         int bits = 1;
         while ((1ll << bits) <= h->ntiles) ++bits;
         alloc(sscr, radix_sort_scratch_bytes(h->npieces), "piece sort");
-        check(radix_sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), h->npieces, bits, sscr.p,
+        check(sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), h->npieces, bits, sscr,
                                st),
               "piece sort");
         alloc(h->pieces, h->npieces * sizeof(Piece), "sorted pieces");
@@ -1710,7 +1719,7 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
                                      vv.as<uint32_t>(), st),
                   "V pieces");
             alloc(vs, radix_sort_scratch_bytes(nv), "V piece sort");
-            check(radix_sort_pairs(vk.as<uint64_t>(), vv.as<uint32_t>(), nv, bits, vs.p, st),
+            check(sort_pairs(vk.as<uint64_t>(), vv.as<uint32_t>(), nv, bits, vs, st),
                   "V piece sort");
             vs.release();
             alloc(h->vpieces, (size_t)nv * sizeof(Piece), "sorted V pieces");
@@ -1906,7 +1915,7 @@ void stage_forest(hmx_hmatrix_s* u, int np, const void* const* pts, int pts_f64,
               "morton");
         check(hipMemcpyAsync(keys.p, C.p, (size_t)N * 8, hipMemcpyDeviceToDevice, st), "keys");
         alloc(sscr, radix_sort_scratch_bytes(N), "sort scratch");
-        check(radix_sort_pairs(keys.as<uint64_t>(), u->perm.as<uint32_t>(), N, 64, sscr.p, st),
+        check(sort_pairs(keys.as<uint64_t>(), u->perm.as<uint32_t>(), N, 64, sscr, st),
               "radix sort");
         // stably by problem: every problem's points back in its own range
         int pbits = 1;
@@ -1914,7 +1923,7 @@ void stage_forest(hmx_hmatrix_s* u, int np, const void* const* pts, int pts_f64,
         check(launch_forest_problem_keys(u->perm.as<uint32_t>(), N, np, PB, keys.as<uint64_t>(),
                                          st),
               "problem keys");
-        check(radix_sort_pairs(keys.as<uint64_t>(), u->perm.as<uint32_t>(), N, pbits, sscr.p, st),
+        check(sort_pairs(keys.as<uint64_t>(), u->perm.as<uint32_t>(), N, pbits, sscr, st),
               "problem sort");
         alloc(u->codes, (size_t)N * 8, "morton codes");
         check(launch_gather_u64(C.as<uint64_t>(), u->perm.as<uint32_t>(), N,
@@ -2096,7 +2105,7 @@ void batched_impl(hmx_hmatrix_s* u, int np, const void* const* pts, int pts_f64,
                                   vals.as<uint32_t>(), st),
               "classes");
         alloc(sscr, radix_sort_scratch_bytes(nadm), "class sort");
-        check(radix_sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), nadm, 2, sscr.p, st),
+        check(sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), nadm, 2, sscr, st),
               "class sort");
         DevBuf a2, l2, i2;
         alloc(a2, nadm * sizeof(int4), "adm leaves");
@@ -2182,14 +2191,6 @@ hmx_status guarded(F&& f) {
         return HMX_ERR_OOM;
     }
     return HMX_OK;
-}
-
-// grow a work buffer without keeping its contents (the stream is synchronised
-// first: the old block may still be in use by queued work)
-void ensure(DevBuf& b, size_t bytes, hipStream_t st, const char* what) {
-    if (b.p && b.bytes >= bytes) return;
-    check(hipStreamSynchronize(st), "work buffer sync");
-    alloc(b, bytes, what);
 }
 
 // argument checks shared by hmx_matvec and hmx_matvec_graph

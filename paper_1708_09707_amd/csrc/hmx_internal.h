@@ -295,10 +295,11 @@ hipError_t launch_forest_problem_keys(const uint32_t* idx, int64_t N, int np,
 hipError_t launch_gather_u64(const uint64_t* src, const uint32_t* idx, int64_t n, uint64_t* dst,
                              hipStream_t st);
 // stable LSD radix sort of (key, value) pairs on the low `bits` key bits;
-// scratch from radix_sort_scratch_bytes; results end in keys/vals
+// scratch of at least radix_sort_scratch_bytes(n) (less: hipErrorInvalidValue);
+// results end in keys/vals
 size_t radix_sort_scratch_bytes(int64_t n);
 hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int bits, void* scratch,
-                            hipStream_t st);
+                            size_t scratch_bytes, hipStream_t st);
 hipError_t launch_gather_coords(const void* pts, int pts_f64, int64_t n, int d,
                                 const uint32_t* perm, double* soa64, float* soa32,
                                 hipStream_t st);

@@ -373,8 +373,9 @@ size_t radix_sort_scratch_bytes(int64_t n) {
 }
 
 hipError_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int bits, void* scratch,
-                            hipStream_t st) {
+                            size_t scratch_bytes, hipStream_t st) {
     if (n <= 1 || bits <= 0) return hipSuccess;
+    if (scratch_bytes < radix_sort_scratch_bytes(n)) return hipErrorInvalidValue;
     const int64_t nt = sort_tiles(n);
     char* p = (char*)scratch;
     uint64_t* k2 = (uint64_t*)p;

@@ -167,6 +167,33 @@ static int foreign(const char* name) {
     return 0;
 }
 
+// the work space of a repeated sort out of the cache, whose blocks are up to a third
+// larger than asked: each buffer holds what the count needs, whatever the other does
+static int sort_space(const char* name) {
+    struct Buf { void* p = nullptr; size_t bytes = 0; };
+    for (size_t more = 0; more <= 33; ++more) {
+        Card k;
+        Cache c(Fake{&k});
+        const size_t n0 = 1000000;
+        Block big = take(c, n0 * 8 * (100 + more) / 100);  // what an earlier build left
+        c.free(big.p, big.n);
+        hmx::SortSpace<Buf> s;
+        auto grow = [&](Buf& b, size_t bytes) {
+            if (b.p) c.free(b.p, b.bytes);
+            Block got = take(c, bytes);
+            b.p = got.p;
+            b.bytes = got.n;
+        };
+        for (size_t n = n0; n < n0 * 2; n += n0 / 50) {
+            const size_t keys = n * 8, scratch = n * 12 + n / 10;
+            s.reserve(keys, scratch, grow);
+            EXPECT(s.keys.bytes >= keys);
+            EXPECT(s.scratch.bytes >= scratch);
+        }
+    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const std::string n = argv[1];
     if (n == "sequence") return sequence(argv[1]);
@@ -175,6 +202,7 @@ int main(int argc, char** argv) {
     if (n == "too_large") return too_large(argv[1]);
     if (n == "devices") return devices(argv[1]);
     if (n == "foreign") return foreign(argv[1]);
+    if (n == "sort_space") return sort_space(argv[1]);
     return 2;
 }
 """
@@ -190,7 +218,8 @@ def program(tmp_path_factory):
     return str(d / "t")
 
 
-@pytest.mark.parametrize("case", ["sequence", "reuse", "others", "too_large", "devices", "foreign"])
+@pytest.mark.parametrize("case", ["sequence", "reuse", "others", "too_large", "devices", "foreign",
+                                  "sort_space"])
 def test_block_cache(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout

@@ -99,3 +99,65 @@ def test_oom_at_every_stage_returns_everything(H, symmetric):
     # the library still builds normally afterwards
     h = H.HMatrix(pts, "gaussian", 0.02, symmetric_far=symmetric, **KW)
     h.close()
+
+
+class GuardedAllocator:
+    """TorchAllocator whose blocks end in 64 KB of a known pattern, looked at
+    when they come back."""
+
+    GUARD = 1 << 16
+
+    def __init__(self, H):
+        self.inner = H.TorchAllocator()
+        self.broken = []
+        take, pattern = self.inner.take, 0xA5
+
+        def guarded_take(nbytes):
+            ptr = take(nbytes + self.GUARD)
+            if ptr:
+                self._guard(ptr, nbytes).fill_(pattern)
+            return ptr
+
+        def checked_free(ptr, nbytes, ctx):
+            if not bool((self._guard(ptr, nbytes) == pattern).all()):
+                self.broken.append(int(nbytes))
+            self.inner._free(ptr, nbytes, ctx)
+        self.inner.take = guarded_take
+        self.alloc_fn, self.free_fn = self.inner.alloc_fn, H.FREE_FN(checked_free)
+
+    def _guard(self, ptr, nbytes):
+        class Span:
+            __cuda_array_interface__ = dict(shape=(self.GUARD,), typestr="|u1", version=2,
+                                            data=(int(ptr) + int(nbytes), False))
+        return torch.as_tensor(Span(), device="cuda:0")
+
+
+@pytest.mark.parametrize("symmetric", [0, 1])
+def test_learned_build_keeps_to_its_buffers(H, symmetric):
+    """A learned build in chunks of 1 MB whose targets are too small, so that
+    part of the list is approximated again in chunks of other counts; the
+    result is that of one chunk bit for bit and no buffer is written past its
+    end."""
+    n = 30000
+    pts = _dev(synth.uniform_points(n, 2, 611, dtype=np.float32))
+    x = _dev(synth.normal_vector(n, 612, dtype=np.float32))
+    w = np.zeros(8961, np.float32)
+    w[-1] = 3.0  # predicted rank 3 for every block
+    mlp = H.RankMLP(w)
+    kw = dict(KW, max_rank=12, aca_eps=1e-6, leaf_size=32, symmetric_far=symmetric,
+              rank_mode="learned", mlp=mlp)
+    one = H.HMatrix(pts, "gaussian", 0.01, **kw)
+    want, ranks = one.matvec(x), one.ranks()
+    one.close()
+    a = GuardedAllocator(H)
+    print("learned build, 1 MB chunks, guarded buffers, symmetric %d" % symmetric, flush=True)
+    hm = H.HMatrix(pts, "gaussian", 0.01, allocator=a, aca_chunk_mb=1, **kw)
+    st = hm.stats()
+    print("  %d chunks, %d past the target, %d again" % (st.aca_chunks, st.aca_overflow,
+                                                          st.aca_fallback), flush=True)
+    assert st.aca_chunks > 4 and st.aca_fallback > 0
+    assert np.array_equal(hm.ranks(), ranks)
+    assert torch.equal(hm.matvec(x), want)
+    hm.close()
+    mlp.close()
+    assert a.broken == [] and a.inner.outstanding_bytes == 0
