@@ -70,6 +70,11 @@ constexpr int kP1Threads = 256;
 constexpr int kP1Cols = 16;     // columns per lane group in flight
 constexpr int kP1BufWord3 = 0x00020000;  // 32-bit data format, the raw-buffer form on CDNA
 constexpr int kP1Nt = 2;        // non-temporal: every entry is read once per product
+// rows of a tile up to which a batch's columns are at 32-bit offsets from one
+// descriptor (its 31 bits would hold 2 million FP64 rows with the narrowest groups).
+// A tile of 70001 rows and one of 250000, 24 FP64 columns each: 64-bit addresses
+// 601-607 and 2040-2050 us, offsets 613 and 2079; 16384 rows the same to 1%
+constexpr int kP1Tall = 1 << 16;
 constexpr int kP1Stage = 2048;  // rows of x a tile stages in LDS (taller tiles read x directly)
 
 // Tile pass.  meta[ms * t + 1] = first source column of tile t (tile t + 1's
@@ -92,8 +97,9 @@ constexpr int kP1Stage = 2048;  // rows of x a tile stages in LDS (taller tiles 
 // tiles, 14.9 GB) 3257 and 2543 us (5.9 TB/s); N = 2^14 3-d FP64 (256 tiles, 0.49
 // GB) 143 and 94 us; N = 4096 FP64 (64 tiles) 15 and 10 us; N = 2^19 2-d FP64
 // (6.0 GB) 1133-1176 and 1150-1188 us.
-template <typename S, typename T, int L>
-__global__ __launch_bounds__(kP1Threads, 3) void p1_tile_kernel(
+// WIDE (tiles of more than kP1Tall rows): 64-bit addresses
+template <typename S, typename T, int L, bool WIDE>
+__global__ __launch_bounds__(kP1Threads, WIDE ? 2 : 3) void p1_tile_kernel(
     int64_t ntiles, const int32_t* __restrict__ tile_lo, const int64_t* __restrict__ meta, int ms,
     int R, const S* __restrict__ pool, const T* __restrict__ vec, T* __restrict__ partial,
     int64_t pbase) {
@@ -120,9 +126,6 @@ __global__ __launch_bounds__(kP1Threads, 3) void p1_tile_kernel(
         const S* __restrict__ base = pool + meta[ms * t + 2];
         // x of the tile (rows past it read as zero)
         const bool staged = ld <= kP1Stage;
-        // a batch's span past the descriptor's 31-bit offsets (leaves of
-        // millions of points): one column at a time, 64-bit addresses
-        const bool wide = (int64_t)SUB * kP1Cols * ld * (int64_t)sizeof(S) >= 0x7fffffff;
         if (staged) {
             for (int i = threadIdx.x; i < ld; i += kP1Threads) sx[i] = i < mt ? vec[r0 + i] : (T)0;
             __syncthreads();
@@ -141,30 +144,16 @@ __global__ __launch_bounds__(kP1Threads, 3) void p1_tile_kernel(
             for (int vi = q; vi < nvec; vi += L) {
                 u32x4 raw[kP1Cols];
                 const int row = vi * VS;
-                if (wide) {
-#pragma unroll 1
-                    for (int u = 0; u < kP1Cols; ++u) {
-                        const int cu = cb + u * SUB + sub;
-                        const S* p = base + (int64_t)(cu < nc ? cu : nc - 1) * ld + row;
-                        T a[VS];
-                        P1Dec<S, T>::get(*(const u32x4*)p, a);
-#pragma unroll
-                        for (int e = 0; e < VS; ++e)
-                            a[e] *= row + e < mt ? vec[r0 + row + e] : (T)0;
-                        T sum = a[0];
-#pragma unroll
-                        for (int e = 1; e < VS; ++e) sum += a[e];
-#pragma unroll
-                        for (int v = 0; v < kP1Cols; ++v) acc[v] += v == u ? sum : (T)0;
-                    }
-                    continue;
-                }
 #pragma unroll
                 for (int u = 0; u < kP1Cols; ++u) {
                     const int cu = u * SUB + sub;
                     const int c = cu < last ? cu : last;  // past the end: never stored
-                    raw[u] = __builtin_amdgcn_raw_buffer_load_b128(
-                        rs, (c * ld + row) * (int)sizeof(S), 0, kP1Nt);
+                    if constexpr (WIDE)
+                        raw[u] = __builtin_nontemporal_load(
+                            (const u32x4*)(bp + (int64_t)c * ld + row));
+                    else
+                        raw[u] = __builtin_amdgcn_raw_buffer_load_b128(
+                            rs, (c * ld + row) * (int)sizeof(S), 0, kP1Nt);
                 }
                 T xv[VS];
 #pragma unroll
@@ -465,9 +454,16 @@ hipError_t p1_tile_dispatch(int64_t ntiles, const int32_t* tile_lo, const int64_
     constexpr int64_t kP1Fill = 2048;
     const int64_t split = (kP1Fill + ntiles - 1) / ntiles;
     const dim3 grid(gx, (unsigned)std::max<int64_t>(std::min<int64_t>(split, 16), 1));
-#define HMX_P1(LL)                                                                             \
-    hipLaunchKernelGGL((p1_tile_kernel<S, T, LL>), grid, dim3(kP1Threads), 0, st, ntiles, \
+#define HMX_P1K(LL, WW)                                                                        \
+    hipLaunchKernelGGL((p1_tile_kernel<S, T, LL, WW>), grid, dim3(kP1Threads), 0, st, ntiles,  \
                        tile_lo, meta, ms, R, (const S*)pool, (const T*)vec, (T*)partial, pbase)
+#define HMX_P1(LL)             \
+    do {                       \
+        if (max_ld > kP1Tall)  \
+            HMX_P1K(LL, true); \
+        else                   \
+            HMX_P1K(LL, false); \
+    } while (0)
     if (lanes == 8)
         HMX_P1(8);
     else if (lanes == 16)
@@ -477,6 +473,7 @@ hipError_t p1_tile_dispatch(int64_t ntiles, const int32_t* tile_lo, const int64_
     else
         HMX_P1(64);
 #undef HMX_P1
+#undef HMX_P1K
     return hipGetLastError();
 }
 

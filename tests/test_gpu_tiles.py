@@ -69,3 +69,29 @@ def test_matmat_columns_past_31_bits(H):
     print("  worst column vs matvec: %.2e" % worst, flush=True)
     assert worst <= 1e-13
     hm.close()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("n2", [65536, 65537, 70001])
+def test_source_tiles_past_short_offsets(H, orc, n2, dtype):
+    """One admissible block whose source side is one tile, up to the rows that
+    32-bit offsets serve and past them (64-bit addresses), against the dense
+    FP64 product; bounds as in test_product_over_tiles."""
+    eps, tol, t = {"f64": (1e-9, 1e-8, torch.float64), "f32": (1e-6, 2e-5, torch.float32),
+                   "bf16": (1e-3, 1.2e-2, torch.float32)}[dtype]
+    n1 = 200
+    p1 = synth.uniform_points(n1, 2, 51)
+    p2 = synth.uniform_points(n2, 2, 52)
+    p2[:, 0] += 3.0  # distance >= 2 > diameter: the root block is admissible
+    x = np.random.default_rng(n2).uniform(0.5, 1.5, n2)
+    print("one block %d x %d %s" % (n1, n2, dtype), flush=True)
+    hm = H.HMatrix.rect(torch.from_numpy(p1).to("cuda:0", t), torch.from_numpy(p2).to("cuda:0", t),
+                        "gaussian", 4.0, compute_dtype="f32" if dtype == "bf16" else dtype,
+                        storage_dtype=dtype, leaf_size=1 << 17, eta=1.5, aca_eps=eps, max_rank=64)
+    assert hm.stats().n_adm == 1 and hm.stats().n_dense == 0
+    z = hm.matvec(torch.from_numpy(x).to("cuda:0", t)).double().cpu().numpy()
+    zd = orc.dense_matvec_rect(p1, p2, x, "gaussian", 4.0)
+    err = np.linalg.norm(z - zd) / np.linalg.norm(zd)
+    print("  error %.2e" % err, flush=True)
+    assert err <= tol
+    hm.close()
