@@ -682,7 +682,7 @@ __device__ __forceinline__ void rowtile_segment(const S* __restrict__ base, int 
 // the stored mode's assembly (D = 2 or 3 coordinates, missing ones zero).  Rows
 // past the tile (padding) read the tile's last point and are never written
 // out.  Bound by vector issue: the kernel's kind and dimension are template
-// arguments, so the inner loop is straight-line code whose kEvalUnroll R
+// arguments, so the inner loop is straight-line code whose EU R
 // exponentials overlap, and the LDS of a workgroup leaves room for more of
 // them on a compute unit.  N = 2^17 Halton points, leaf 2048, FP64 Gaussian
 // (2.96e9 entries): 13.8 ms with a branch on the kind per entry, the
@@ -704,6 +704,10 @@ __device__ __forceinline__ void rowtile_near_eval(const T* __restrict__ soa, int
             i = i < rows ? i : rows - 1;
             load_pt(soa, n, d, row0 + i, xr[v][e]);
         }
+    // (32 rows a lane: their coordinates leave registers for two columns; four put
+    // 400 bytes a lane into private memory, 1.74 against 1.93 ms for 30000 points
+    // with leaves of 1000, and 16.0 with a branch on the kind per entry)
+    constexpr int EU = RV * R >= 32 ? 2 : kEvalUnroll;
     for (int64_t kc = 0; kc < nk; kc += kEvalChunk) {
         const int cnt = (nk - kc) < kEvalChunk ? (int)(nk - kc) : kEvalChunk;
         for (int j = threadIdx.x; j < cnt; j += kTileThreads) {
@@ -713,13 +717,13 @@ __device__ __forceinline__ void rowtile_near_eval(const T* __restrict__ soa, int
             for (int k = 0; k < D; ++k) sy[k * kEvalChunk + j] = k < d ? soa[(int64_t)k * n + w] : (T)0;
         }
         __syncthreads();
-        // kEvalUnroll columns per iteration: their LDS reads are issued
+        // EU columns per iteration: their LDS reads are issued
         // together and the entries' exponentials overlap
         int c = g;
-        for (; c + (kEvalUnroll - 1) * G < cnt; c += kEvalUnroll * G) {
-            T w[kEvalUnroll], y[kEvalUnroll][3];
+        for (; c + (EU - 1) * G < cnt; c += EU * G) {
+            T w[EU], y[EU][3];
 #pragma unroll
-            for (int u = 0; u < kEvalUnroll; ++u) {
+            for (int u = 0; u < EU; ++u) {
                 const int cc = c + u * G;
                 w[u] = sw[cc];
 #pragma unroll
@@ -729,7 +733,7 @@ __device__ __forceinline__ void rowtile_near_eval(const T* __restrict__ soa, int
             for (int v = 0; v < RV; ++v) {
                 if (v * L + q < nvec) {
 #pragma unroll
-                    for (int u = 0; u < kEvalUnroll; ++u)
+                    for (int u = 0; u < EU; ++u)
 #pragma unroll
                         for (int e = 0; e < R; ++e)
                             acc[v][e] += phi_kind<KIND, true>(K, xr[v][e], y[u]) * w[u];
