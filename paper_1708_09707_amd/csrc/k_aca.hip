@@ -331,14 +331,29 @@ __device__ double block_sum(double a, AcaShared<T, NW>& sh, int slot) {
     return s;
 }
 
+// the smallest value of the wave, on every lane
+__device__ __forceinline__ int wave_min(int v) {
+    int u = dpp<kDppXor1>(v);
+    v = u < v ? u : v;
+    u = dpp<kDppXor2>(v);
+    v = u < v ? u : v;
+    u = dpp<kDppHalfMirror>(v);
+    v = u < v ? u : v;
+    u = dpp<kDppMirror>(v);
+    v = u < v ? u : v;
+    int r = lane_read(v, 0);
+#pragma unroll
+    for (int q = 16; q < 64; q += 16) {
+        const int t = lane_read(v, q);
+        r = t < r ? t : r;
+    }
+    return r;
+}
+
 template <typename T, int NW>
 __device__ int block_min_int(int v, AcaShared<T, NW>& sh) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        int u = __shfl_xor(v, o, 64);
-        v = u < v ? u : v;
-    }
+    v = wave_min(v);
     if (lane == 0) sh.imin[w] = v;
     __syncthreads();
     int r = sh.imin[0];
@@ -421,7 +436,9 @@ __device__ int first_column(const double* __restrict__ soa64, int64_t n, int d, 
                             AcaShared<T, NT / kWave>& sh) {
     const int m = bl.y - bl.x, nc = bl.w - bl.z;
     double c[3] = {0.0, 0.0, 0.0};
-    for (int k = 0; k < d; ++k) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (k >= d) break;
         double mn = INFINITY, mx = -INFINITY;
         for (int i = threadIdx.x; i < m; i += NT) {
             const double v = soa64[(int64_t)k * n + bl.x + i];
@@ -436,7 +453,9 @@ __device__ int first_column(const double* __restrict__ soa64, int64_t n, int d, 
     int bi = INT_MAX;
     for (int q = threadIdx.x; q < nc; q += NT) {
         double s = 0.0;
-        for (int k = 0; k < d; ++k) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (k >= d) break;
             const double t = __dsub_rn(soa64[(int64_t)k * n + bl.z + q], c[k]);
             s = __dadd_rn(s, __dmul_rn(t, t));
         }
@@ -497,6 +516,17 @@ __device__ __forceinline__ void clamp_rows(int i0, int len, int (&ic)[KR], bool 
 template <typename T>
 __device__ __forceinline__ T ld_at(const T* __restrict__ base, uint32_t byte_off) {
     return *(const T*)((const char*)base + byte_off);
+}
+
+template <typename T>
+__device__ __forceinline__ void st_at(T* __restrict__ base, uint32_t byte_off, T v) {
+    *(T*)((char*)base + byte_off) = v;
+}
+// v, as a value the compiler knows nothing of: addresses formed from it are
+// formed where they are used, not kept over the whole step loop
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
 // Loads through a raw buffer descriptor on a wave-uniform base: the per-lane
@@ -664,8 +694,7 @@ __device__ __forceinline__ long long uniform_i64(long long v) {
 // A block of the learned sizing pass that reached its target unfinished:
 // request R columns of overflow storage (one atomic, by thread 0), copy the
 // r columns computed so far and return the offset granted (the same on every
-// thread), or -1 when the reserve is exhausted.  Kept out of line: the step
-// loop's code stays compact.
+// thread), or -1 when the reserve is exhausted.
 template <typename T, int NT>
 __device__ __forceinline__ long long aca_overflow_move(const Overflow& ovf, int m, int nc, int R, int r,
                                                     const T* __restrict__ U,
@@ -682,17 +711,23 @@ __device__ __forceinline__ long long aca_overflow_move(const Overflow& ovf, int 
     if (off < 0) return -1;
     T* __restrict__ Un = Upool + (ovf.u0 + off - ubase);
     T* __restrict__ Vn = Vpool + (ovf.v0 + off - vbase);
-    for (int e = threadIdx.x; e < r * m; e += NT) Un[e] = U[e];
-    for (int e = threadIdx.x; e < r * nc; e += NT) Vn[e] = V[e];
+    const int t = opaque(threadIdx.x);
+    for (int e = t; e < r * m; e += NT) Un[e] = U[e];
+    for (int e = t; e < r * nc; e += NT) Vn[e] = V[e];
     __syncthreads();
     return off;
 }
 
 // waves per SIMD the compiler must leave room for: four in FP32 (the steps
-// wait on loads, and gain more from the occupancy than the 176 spilled bytes
-// per lane cost: eight rows a thread at two waves, without spills, took 46 ms
-// instead of 29 for the blocks above 4096 points at N = 2^20), two in FP64,
-// whose values take twice the registers
+// wait on loads, and gain from the occupancy: eight rows a thread at two waves
+// took 46 ms instead of 29 for the blocks above 4096 points at N = 2^20), two in
+// FP64, whose values take twice the registers.  All values of a step fit these
+// registers: the runtime has to map a kernel's private memory at its launch, on
+// a card that may be full.  Uniform values are said to be (scalar registers), a
+// workgroup has one block and no loop around it, addresses are 32-bit offsets or
+// formed where they are used.  With 176 bytes a lane in private memory (FP32; FP64
+// 48) the ACA phase took 29.7 ms at N = 2^20 2-d FP32, now 29.1; 28.2 and 27.8-28.5
+// at N = 2^19 2-d FP64; 27.8 and 27.6 at N = 100003 3-d FP32.
 template <typename T>
 constexpr int aca_min_waves() {
     return sizeof(T) == 8 ? 2 : 4;
@@ -714,365 +749,375 @@ __global__ __launch_bounds__(NT, (aca_min_waves<T>())) void aca_kernel(
     __shared__ double accu[NW][kMaxRankCap];  // deferred products, one row per wave
     __shared__ double accv[NW][kMaxRankCap];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const double tol = eps * (1.0 - aca_eta) / (1.0 + eps);
+    const double tol = lane_read(eps * (1.0 - aca_eta) / (1.0 + eps), 0);
 
-    for (int64_t o = blockIdx.x; o < nblocks; o += gridDim.x) {
-        const int64_t b = order[o];
-        const int4 bl = blocks[b];
-        const int m = bl.y - bl.x, nc = bl.w - bl.z;
-        int R = kmax;
-        R = m < R ? m : R;
-        R = nc < R ? nc : R;
-        // the block's storage offsets live in LDS and are read at every step
-        // (they move once if the block outgrows its target into overflow
-        // storage; a loop-carried pointer would cost the loop its hoisting)
+    if ((int64_t)blockIdx.x >= nblocks) return;
+    const int64_t b = order[blockIdx.x];
+    const int4 bl = blocks[b];
+    const int m = bl.y - bl.x, nc = bl.w - bl.z;
+    int R = kmax;
+    R = m < R ? m : R;
+    R = nc < R ? nc : R;
+    // the block's storage offsets live in LDS and are read at every step
+    // (they move once if the block outgrows its target into overflow
+    // storage; a loop-carried pointer would cost the loop its hoisting)
+    if (tid == 0) {
+        sh.uo = uoff[b] - ubase;
+        sh.vo = voff[b] - vbase;
+    }
+    const BufView<T> rows_pts(soa + bl.x), cols_pts(soa + bl.z);
+    const int mw = (m + 31) >> 5, nw = (nc + 31) >> 5;
+    const bool single = m <= KR * NT;  // one pass covers every row
+    if (mw + nw > lds_words) {  // outside this launch's size class (never by construction)
         if (tid == 0) {
-            sh.uo = uoff[b] - ubase;
-            sh.vo = voff[b] - vbase;
+            rank_out[b] = 0;
+            if (steps_out) steps_out[b] = 0;
         }
-        const BufView<T> rows_pts(soa + bl.x), cols_pts(soa + bl.z);
-        const int mw = (m + 31) >> 5, nw = (nc + 31) >> 5;
-        const bool single = m <= KR * NT;  // one pass covers every row
-        if (mw + nw > lds_words) {  // outside this launch's size class (never by construction)
-            if (tid == 0) {
-                rank_out[b] = 0;
-                if (steps_out) steps_out[b] = 0;
-            }
-            continue;
-        }
-        uint32_t* rmask = smask;
-        uint32_t* cmask = smask + mw;
-        for (int q = tid; q < mw + nw; q += NT) smask[q] = 0u;
-        __syncthreads();
+        return;
+    }
+    uint32_t* rmask = smask;
+    uint32_t* cmask = smask + mw;
+    for (int q = tid; q < mw + nw; q += NT) smask[q] = 0u;
+    __syncthreads();
 
-        // rtarget[b] > 0 bounds the block's columns to a predicted target.
-        // Sizing form (one_shot_mode = 0): the stopping test runs every step
-        // as in the adaptive method.  One-shot form: the target is reached
-        // without the test, which then judges the last term.  A block that
-        // reaches its target unfinished either continues adaptively (storage
-        // for k_max columns) or, with cap_only (storage for the target only),
-        // ends with rank -1 to be approximated again with k_max columns.
-        const bool sized = rtarget && rtarget[b] > 0;
-        bool one_shot = sized && one_shot_mode;
-        int target = sized ? (rtarget[b] < R ? rtarget[b] : R) : R;
-        bool refused = false;
-        double last_p = 0.0;  // |u_r|^2 |v_r|^2 of the last term
-        // With the test applied every step, term p's products with the
-        // earlier terms are gathered while the passes of term p + 1 read
-        // those columns anyway; term p's test is taken once they are
-        // complete, and term p + 1 is dropped if it passes (it was computed
-        // speculatively).  The decisions are those of the step-by-step order.
-        const bool fuse = !fixed && !one_shot;
-        bool pending = false;     // term r - 1's test is still open
-        double nu2p = 0.0, nv2p = 0.0;
+    // rtarget[b] > 0 bounds the block's columns to a predicted target.
+    // Sizing form (one_shot_mode = 0): the stopping test runs every step
+    // as in the adaptive method.  One-shot form: the target is reached
+    // without the test, which then judges the last term.  A block that
+    // reaches its target unfinished either continues adaptively (storage
+    // for k_max columns) or, with cap_only (storage for the target only),
+    // ends with rank -1 to be approximated again with k_max columns.
+    const bool sized = rtarget && rtarget[b] > 0;
+    bool one_shot = sized && one_shot_mode;
+    int target = sized ? (rtarget[b] < R ? rtarget[b] : R) : R;
+    bool refused = false;
+    double last_p = 0.0;  // |u_r|^2 |v_r|^2 of the last term
+    // With the test applied every step, term p's products with the
+    // earlier terms are gathered while the passes of term p + 1 read
+    // those columns anyway; term p's test is taken once they are
+    // complete, and term p + 1 is dropped if it passes (it was computed
+    // speculatively).  The decisions are those of the step-by-step order.
+    const bool fuse = !fixed && !one_shot;
+    bool pending = false;     // term r - 1's test is still open
+    double nu2p = 0.0, nv2p = 0.0;
 
-        int r = 0, ncols_used = 0, nfailed = 0, steps = 0;
-        int j = first_column<T, NT>(soa64, n, d, bl, sh);  // (its barriers publish sh.uo, sh.vo)
-        double S2 = 0.0;
-        for (;;) {
-            if (r >= target) {
-                if (r >= R) break;
-                if (one_shot) {
-                    one_shot = false;
-                    if (sqrt(last_p) <= tol * sqrt(S2)) break;
-                }
-                if (pending) {
-                    // no room for a speculative term: term r - 1's products now,
-                    // summed in the order of the deferred accumulation
-                    column_products_waved<T, NT, KR>(Upool + uniform_i64(sh.uo), m, r - 1, accu);
-                    column_products_waved<T, NT, KR>(Vpool + uniform_i64(sh.vo), nc, r - 1, accv);
-                    double cross = 0.0;
-                    for (int l = 0; l < r - 1; ++l) {
-                        double gu = accu[0][l], gv = accv[0][l];
-                        for (int q = 1; q < NW; ++q) {
-                            gu += accu[q][l];
-                            gv += accv[q][l];
-                        }
-                        cross += gu * gv;
-                    }
-                    __syncthreads();  // every wave has read the rows before any clears them
-                    S2 += 2.0 * cross + nu2p * nv2p;
-                    last_p = nu2p * nv2p;
-                    pending = false;
-                    if (sqrt(last_p) <= tol * sqrt(S2)) break;
-                }
-                if (cap_only) {
-                    // storage for the target only: continue in overflow
-                    // storage for R columns if the reserve has room
-                    const long long off = uniform_i64(
-                        ovf.used ? aca_overflow_move<T, NT>(ovf, m, nc, R, r,
-                                                            Upool + uniform_i64(sh.uo),
-                                                            Vpool + uniform_i64(sh.vo), Upool,
-                                                            Vpool, ubase, vbase, &sh.ovf)
-                                 : -1);
-                    if (off < 0) {
-                        refused = true;
-                        break;
-                    }
-                    if (tid == 0) {
-                        sh.uo = ovf.u0 + off - ubase;
-                        sh.vo = ovf.v0 + off - vbase;
-                        ovf.moved[b] = off;
-                    }
-                    __syncthreads();
-                }
-                target = R;
+    int r = 0, ncols_used = 0, nfailed = 0, steps = 0;
+    int j = first_column<T, NT>(soa64, n, d, bl, sh);  // (its barriers publish sh.uo, sh.vo)
+    double S2 = 0.0;
+    for (;;) {
+        if (r >= target) {
+            if (r >= R) break;
+            if (one_shot) {
+                one_shot = false;
+                if (sqrt(last_p) <= tol * sqrt(S2)) break;
             }
-            // columns l < r are only read in a step, column r only written
-            T* __restrict__ U = Upool + uniform_i64(sh.uo);
-            T* __restrict__ V = Vpool + uniform_i64(sh.vo);
-            const T* __restrict__ Uread = U;
-            const T* __restrict__ Vread = V;
-            const int p = r - 1;  // the open term, when pending
-            // ---- step 1: residual column j into U[:, r] ----
-            for (int l = tid; l < r; l += NT) sh.vec[l] = V[(int64_t)l * nc + j];
-            if (tid == 0) cmask[j >> 5] |= 1u << (j & 31);
-            if (pending)
-                for (int l = lane; l < p; l += kWave) {
-                    accu[w][l] = 0.0;
-                    accv[w][l] = 0.0;
-                }
-            __syncthreads();
-            ++ncols_used;
-            ++steps;
-            T yj[3];
-            load_pt(soa, n, d, (int64_t)bl.z + j, yj);
-            Arg<T> am{(T)-1, INT_MAX, (T)0};
-            double colmax = 0.0;
-            T keep[KR];  // the residual column itself when the block has one pass of rows
-            // KR rows per thread per pass; the trip count is the same for
-            // every thread of the workgroup
-            for (int ib = 0; ib < m; ib += KR * NT) {
-                int ic[KR];
-                bool ok[KR];
-                clamp_rows<NT, KR>(ib + tid, m, ic, ok);
-                T xi[KR][3], a[KR], up[KR];
-#pragma unroll
-                for (int k = 0; k < KR; ++k) {
-                    const uint32_t off = (uint32_t)ic[k] * (uint32_t)sizeof(T);
-                    load_pt_buf(rows_pts, n, d, off, xi[k]);
-                    up[k] = (T)0;
-                    if (pending) {
-                        const T v = ld_at(Uread + (int64_t)p * m, off);
-                        up[k] = ok[k] ? v : (T)0;
-                    }
-                }
-                phi_rows<T, KR>(K, xi, yj, a);
-#pragma unroll
-                for (int k = 0; k < KR; ++k) {
-                    a[k] = ok[k] ? a[k] : (T)0;
-                    const double aa0 = a[k] < (T)0 ? -(double)a[k] : (double)a[k];
-                    colmax = aa0 > colmax ? aa0 : colmax;
-                }
-                subtract_columns(Uread, m, r, sh.vec, ic, a, pending, p, up, accu[w], lane);
-#pragma unroll
-                for (int k = 0; k < KR; ++k) {
-                    keep[k] = a[k];
-                    if (ok[k]) {
-                        const int i = ic[k];
-                        if (!single) U[(int64_t)r * m + i] = a[k];
-                        const T aa = a[k] < (T)0 ? -a[k] : a[k];
-                        if (!bit_get(rmask, i) && aa > am.best) {
-                            am.best = aa;
-                            am.idx = i;
-                            am.val = a[k];
-                        }
-                    }
-                }
-            }
-            // row pivot and the column's largest |entry| in one reduction
-            am = wave_argmax_u(am);
-            colmax = wave_max(colmax);
-            if constexpr (NW > 1) {
-                if (lane == 0) {
-                    sh.abest[w] = am.best;
-                    sh.aidx[w] = am.idx;
-                    sh.aval[w] = am.val;
-                    sh.dkey[w] = colmax;
-                }
-                __syncthreads();
-                am = Arg<T>{sh.abest[0], sh.aidx[0], sh.aval[0]};
-                colmax = sh.dkey[0];
-                for (int q = 1; q < NW; ++q) {
-                    arg_combine(am, Arg<T>{sh.abest[q], sh.aidx[q], sh.aval[q]});
-                    colmax = sh.dkey[q] > colmax ? sh.dkey[q] : colmax;
-                }
-                __syncthreads();
-            }
-            if (am.idx == INT_MAX || (double)am.best <= (double)eps0 * colmax) {
-                // no usable pivot in this column: try the lowest unused column
-                ++nfailed;
-                if (ncols_used >= nc || nfailed >= kmax) break;
-                int cand = INT_MAX;
-                for (int q = tid; q < nw; q += NT) {
-                    const uint32_t word = cmask[q];
-                    if (word != 0xffffffffu) {
-                        const int c = (q << 5) + __ffs(~word) - 1;
-                        if (c < nc && c < cand) cand = c;
-                    }
-                }
-                cand = block_min_int(cand, sh);
-                if (cand == INT_MAX) break;
-                j = cand;
-                continue;
-            }
-            const int ip = am.idx;
-            const T piv = am.val;
-            // ---- step 3a: u_r = u^ / pivot; |u_r|^2 is reduced with the row's sums ----
-            double nu2 = 0.0;
-            T* __restrict__ Ur = U + (int64_t)r * m;
-            if (single) {
-                int ic[KR];
-                bool ok[KR];
-                clamp_rows<NT, KR>(tid, m, ic, ok);
-#pragma unroll
-                for (int k = 0; k < KR; ++k) {
-                    if (ok[k]) {
-                        const T u = keep[k] / piv;
-                        Ur[ic[k]] = u;
-                        nu2 += (double)u * (double)u;
-                    }
-                }
-            } else {
-                for (int ib = 0; ib < m; ib += KR * NT) {
-                    int ic[KR];
-                    bool ok[KR];
-                    clamp_rows<NT, KR>(ib + tid, m, ic, ok);
-                    T u[KR];
-#pragma unroll
-                    for (int k = 0; k < KR; ++k)
-                        u[k] = ld_at(Ur, (uint32_t)ic[k] * (uint32_t)sizeof(T));
-#pragma unroll
-                    for (int k = 0; k < KR; ++k) {
-                        if (ok[k]) {
-                            u[k] = u[k] / piv;
-                            Ur[ic[k]] = u[k];
-                            nu2 += (double)u[k] * (double)u[k];
-                        }
-                    }
-                }
-            }
-            if (!fuse && !fixed) column_products<T, NT, DC>(Uread, m, r, sh.gu, sh);
-            for (int l = tid; l < r; l += NT) sh.vec[l] = U[(int64_t)l * m + ip];
-            if (tid == 0) rmask[ip >> 5] |= 1u << (ip & 31);
-            __syncthreads();
-            // ---- step 3b: residual row i_r into V[:, r] ----
-            T xp[3];
-            load_pt(soa, n, d, (int64_t)bl.x + ip, xp);
-            double nv2 = 0.0;
-            Arg<T> cm{(T)-1, INT_MAX, (T)0};
-            for (int qb = 0; qb < nc; qb += KR * NT) {
-                int ic[KR];
-                bool ok[KR];
-                clamp_rows<NT, KR>(qb + tid, nc, ic, ok);
-                T yq[KR][3], a[KR], vp[KR];
-#pragma unroll
-                for (int k = 0; k < KR; ++k) {
-                    const uint32_t off = (uint32_t)ic[k] * (uint32_t)sizeof(T);
-                    load_pt_buf(cols_pts, n, d, off, yq[k]);
-                    vp[k] = (T)0;
-                    if (pending) {
-                        const T v = ld_at(Vread + (int64_t)p * nc, off);
-                        vp[k] = ok[k] ? v : (T)0;
-                    }
-                }
-                phi_rows<T, KR>(K, yq, xp, a);
-#pragma unroll
-                for (int k = 0; k < KR; ++k) a[k] = ok[k] ? a[k] : (T)0;
-                subtract_columns(Vread, nc, r, sh.vec, ic, a, pending, p, vp, accv[w], lane);
-#pragma unroll
-                for (int k = 0; k < KR; ++k) {
-                    if (ok[k]) {
-                        const int q = ic[k];
-                        V[(int64_t)r * nc + q] = a[k];
-                        nv2 += (double)a[k] * (double)a[k];
-                        const T aa = a[k] < (T)0 ? -a[k] : a[k];
-                        if (!bit_get(cmask, q) && aa > cm.best) {
-                            cm.best = aa;
-                            cm.idx = q;
-                            cm.val = a[k];
-                        }
-                    }
-                }
-            }
-            // next column pivot, |u_r|^2, |v_r|^2 and (term p's products being
-            // complete) the cross sum of term p, in one reduction; the rows of
-            // the deferred products are read before its closing barrier so
-            // that no wave clears them for the next step while another reads
-            cm = wave_argmax_u(cm);
-            nu2 = wave_total(nu2);
-            nv2 = wave_total(nv2);
-            if constexpr (NW > 1) {
-                if (lane == 0) {
-                    sh.abest[w] = cm.best;
-                    sh.aidx[w] = cm.idx;
-                    sh.aval[w] = cm.val;
-                    sh.dsum[0][w] = nu2;
-                    sh.dsum[1][w] = nv2;
-                }
-                __syncthreads();
-                cm = Arg<T>{sh.abest[0], sh.aidx[0], sh.aval[0]};
-                nu2 = sh.dsum[0][0];
-                nv2 = sh.dsum[1][0];
-                for (int q = 1; q < NW; ++q) {
-                    arg_combine(cm, Arg<T>{sh.abest[q], sh.aidx[q], sh.aval[q]});
-                    nu2 += sh.dsum[0][q];
-                    nv2 += sh.dsum[1][q];
-                }
-            }
-            double cross_p = 0.0;
             if (pending) {
-                for (int l = 0; l < p; ++l) {
+                // no room for a speculative term: term r - 1's products now,
+                // summed in the order of the deferred accumulation
+                column_products_waved<T, NT, KR>(Upool + uniform_i64(sh.uo), m, r - 1, accu);
+                column_products_waved<T, NT, KR>(Vpool + uniform_i64(sh.vo), nc, r - 1, accv);
+                double cross = 0.0;
+                for (int l = 0; l < r - 1; ++l) {
                     double gu = accu[0][l], gv = accv[0][l];
+#pragma unroll 4
                     for (int q = 1; q < NW; ++q) {
                         gu += accu[q][l];
                         gv += accv[q][l];
                     }
-                    cross_p += gu * gv;
+                    cross += gu * gv;
+                }
+                __syncthreads();  // every wave has read the rows before any clears them
+                S2 += 2.0 * cross + nu2p * nv2p;
+                last_p = nu2p * nv2p;
+                pending = false;
+                if (sqrt(last_p) <= tol * sqrt(S2)) break;
+            }
+            if (cap_only) {
+                // storage for the target only: continue in overflow
+                // storage for R columns if the reserve has room
+                const long long off = uniform_i64(
+                    ovf.used ? aca_overflow_move<T, NT>(ovf, m, nc, R, r,
+                                                        Upool + uniform_i64(sh.uo),
+                                                        Vpool + uniform_i64(sh.vo), Upool,
+                                                        Vpool, ubase, vbase, &sh.ovf)
+                             : -1);
+                if (off < 0) {
+                    refused = true;
+                    break;
+                }
+                if (tid == 0) {
+                    sh.uo = ovf.u0 + off - ubase;
+                    sh.vo = ovf.v0 + off - vbase;
+                    ovf.moved[b] = off;
+                }
+                __syncthreads();
+            }
+            target = R;
+        }
+        // the same on every lane; saying so keeps them in scalar registers
+        r = __builtin_amdgcn_readfirstlane(r);
+        j = __builtin_amdgcn_readfirstlane(j);
+        S2 = lane_read(S2, 0);
+        nu2p = lane_read(nu2p, 0);
+        nv2p = lane_read(nv2p, 0);
+        last_p = lane_read(last_p, 0);
+        // columns l < r are only read in a step, column r only written
+        T* __restrict__ U = Upool + uniform_i64(sh.uo);
+        T* __restrict__ V = Vpool + uniform_i64(sh.vo);
+        const T* __restrict__ Uread = U;
+        const T* __restrict__ Vread = V;
+        const int p = r - 1;  // the open term, when pending
+        // ---- step 1: residual column j into U[:, r] ----
+        for (int l = opaque(tid); l < r; l += NT) sh.vec[l] = V[(int64_t)l * nc + j];
+        if (tid == 0) cmask[j >> 5] |= 1u << (j & 31);
+        if (pending)
+            for (int l = lane; l < p; l += kWave) {
+                accu[w][l] = 0.0;
+                accv[w][l] = 0.0;
+            }
+        __syncthreads();
+        ++ncols_used;
+        ++steps;
+        T yj[3];
+        load_pt(soa, n, d, (int64_t)bl.z + j, yj);
+        Arg<T> am{(T)-1, INT_MAX, (T)0};
+        double colmax = 0.0;
+        T keep[KR];  // the residual column itself when the block has one pass of rows
+        // KR rows per thread per pass; the trip count is the same for
+        // every thread of the workgroup
+        for (int ib = 0; ib < m; ib += KR * NT) {
+            int ic[KR];
+            bool ok[KR];
+            clamp_rows<NT, KR>(ib + tid, m, ic, ok);
+            T xi[KR][3], a[KR], up[KR];
+#pragma unroll
+            for (int k = 0; k < KR; ++k) {
+                const uint32_t off = (uint32_t)ic[k] * (uint32_t)sizeof(T);
+                load_pt_buf(rows_pts, n, d, off, xi[k]);
+                up[k] = (T)0;
+                if (pending) {
+                    const T v = ld_at(Uread + (int64_t)p * m, off);
+                    up[k] = ok[k] ? v : (T)0;
                 }
             }
-            if constexpr (NW > 1) __syncthreads();
-            // ---- step 4: the norm recursion and the stopping test ----
-            ++r;
-            if (!fuse) {
-                double cross = 0.0;
-                if (!fixed) {
-                    column_products<T, NT, DC>(Vread, nc, r - 1, sh.gv, sh);
-                    for (int l = 0; l < r - 1; ++l) cross += sh.gu[l] * sh.gv[l];
-                }
-                S2 += 2.0 * cross + nu2 * nv2;
-                last_p = nu2 * nv2;
-                if (!fixed && !one_shot && sqrt(last_p) <= tol * sqrt(S2)) break;
-            } else {
-                if (pending) {
-                    // term r - 2 = p, its products summed over the waves in order
-                    S2 += 2.0 * cross_p + nu2p * nv2p;
-                    last_p = nu2p * nv2p;
-                    if (sqrt(last_p) <= tol * sqrt(S2)) {
-                        r -= 1;  // the speculative term is dropped
-                        break;
+            phi_rows<T, KR>(K, xi, yj, a);
+#pragma unroll
+            for (int k = 0; k < KR; ++k) {
+                a[k] = ok[k] ? a[k] : (T)0;
+                const double aa0 = a[k] < (T)0 ? -(double)a[k] : (double)a[k];
+                colmax = aa0 > colmax ? aa0 : colmax;
+            }
+            subtract_columns(Uread, m, r, sh.vec, ic, a, pending, p, up, accu[w], lane);
+#pragma unroll
+            for (int k = 0; k < KR; ++k) {
+                keep[k] = a[k];
+                if (ok[k]) {
+                    const int i = ic[k];
+                    if (!single)
+                            st_at(U + (int64_t)r * m, (uint32_t)i * (uint32_t)sizeof(T), a[k]);
+                    const T aa = a[k] < (T)0 ? -a[k] : a[k];
+                    if (!bit_get(rmask, i) && aa > am.best) {
+                        am.best = aa;
+                        am.idx = i;
+                        am.val = a[k];
                     }
                 }
-                if (r == 1) {  // the first term has no products
-                    S2 = nu2 * nv2;
-                    last_p = S2;
-                    pending = false;
-                    if (sqrt(last_p) <= tol * sqrt(S2)) break;
-                } else {
-                    pending = true;
-                    nu2p = nu2;
-                    nv2p = nv2;
+            }
+        }
+        // row pivot and the column's largest |entry| in one reduction
+        am = wave_argmax_u(am);
+        colmax = wave_max(colmax);
+        if constexpr (NW > 1) {
+            if (lane == 0) {
+                sh.abest[w] = am.best;
+                sh.aidx[w] = am.idx;
+                sh.aval[w] = am.val;
+                sh.dkey[w] = colmax;
+            }
+            __syncthreads();
+            am = Arg<T>{sh.abest[0], sh.aidx[0], sh.aval[0]};
+            colmax = sh.dkey[0];
+#pragma unroll 4
+            for (int q = 1; q < NW; ++q) {
+                arg_combine(am, Arg<T>{sh.abest[q], sh.aidx[q], sh.aval[q]});
+                colmax = sh.dkey[q] > colmax ? sh.dkey[q] : colmax;
+            }
+            __syncthreads();
+        }
+        if (am.idx == INT_MAX || (double)am.best <= (double)eps0 * colmax) {
+            // no usable pivot in this column: try the lowest unused column
+            ++nfailed;
+            if (ncols_used >= nc || nfailed >= kmax) break;
+            int cand = INT_MAX;
+            for (int q = tid; q < nw; q += NT) {
+                const uint32_t word = cmask[q];
+                if (word != 0xffffffffu) {
+                    const int c = (q << 5) + __ffs(~word) - 1;
+                    if (c < nc && c < cand) cand = c;
                 }
             }
-            // ---- step 6: next column pivot ----
-            if (cm.idx == INT_MAX) break;
-            j = cm.idx;
+            cand = block_min_int(cand, sh);
+            if (cand == INT_MAX) break;
+            j = cand;
+            continue;
         }
-        if (tid == 0) {
-            rank_out[b] = refused ? -1 : r;
-            if (steps_out) steps_out[b] = steps;
+        const int ip = __builtin_amdgcn_readfirstlane(am.idx);
+        const T piv = lane_read(am.val, 0);
+        // ---- step 3a: u_r = u^ / pivot; |u_r|^2 is reduced with the row's sums ----
+        double nu2 = 0.0;
+        T* __restrict__ Ur = U + (int64_t)r * m;
+        if (single) {
+            int ic[KR];
+            bool ok[KR];
+            clamp_rows<NT, KR>(opaque(tid), m, ic, ok);
+#pragma unroll
+            for (int k = 0; k < KR; ++k) {
+                if (ok[k]) {
+                    const T u = keep[k] / piv;
+                    st_at(Ur, (uint32_t)ic[k] * (uint32_t)sizeof(T), u);
+                    nu2 += (double)u * (double)u;
+                }
+            }
+        } else {
+            for (int ib = 0; ib < m; ib += KR * NT) {
+                int ic[KR];
+                bool ok[KR];
+                clamp_rows<NT, KR>(ib + tid, m, ic, ok);
+                T u[KR];
+#pragma unroll
+                for (int k = 0; k < KR; ++k)
+                    u[k] = ld_at(Ur, (uint32_t)ic[k] * (uint32_t)sizeof(T));
+#pragma unroll
+                for (int k = 0; k < KR; ++k) {
+                    if (ok[k]) {
+                        u[k] = u[k] / piv;
+                        st_at(Ur, (uint32_t)ic[k] * (uint32_t)sizeof(T), u[k]);
+                        nu2 += (double)u[k] * (double)u[k];
+                    }
+                }
+            }
         }
+        if (!fuse && !fixed) column_products<T, NT, DC>(Uread, m, r, sh.gu, sh);
+        for (int l = opaque(tid); l < r; l += NT) sh.vec[l] = U[(int64_t)l * m + ip];
+        if (tid == 0) rmask[ip >> 5] |= 1u << (ip & 31);
         __syncthreads();
+        // ---- step 3b: residual row i_r into V[:, r] ----
+        T xp[3];
+        load_pt(soa, n, d, (int64_t)bl.x + ip, xp);
+        double nv2 = 0.0;
+        Arg<T> cm{(T)-1, INT_MAX, (T)0};
+        for (int qb = 0; qb < nc; qb += KR * NT) {
+            int ic[KR];
+            bool ok[KR];
+            clamp_rows<NT, KR>(qb + tid, nc, ic, ok);
+            T yq[KR][3], a[KR], vp[KR];
+#pragma unroll
+            for (int k = 0; k < KR; ++k) {
+                const uint32_t off = (uint32_t)ic[k] * (uint32_t)sizeof(T);
+                load_pt_buf(cols_pts, n, d, off, yq[k]);
+                vp[k] = (T)0;
+                if (pending) {
+                    const T v = ld_at(Vread + (int64_t)p * nc, off);
+                    vp[k] = ok[k] ? v : (T)0;
+                }
+            }
+            phi_rows<T, KR>(K, yq, xp, a);
+#pragma unroll
+            for (int k = 0; k < KR; ++k) a[k] = ok[k] ? a[k] : (T)0;
+            subtract_columns(Vread, nc, r, sh.vec, ic, a, pending, p, vp, accv[w], lane);
+#pragma unroll
+            for (int k = 0; k < KR; ++k) {
+                if (ok[k]) {
+                    const int q = ic[k];
+                    st_at(V + (int64_t)r * nc, (uint32_t)q * (uint32_t)sizeof(T), a[k]);
+                    nv2 += (double)a[k] * (double)a[k];
+                    const T aa = a[k] < (T)0 ? -a[k] : a[k];
+                    if (!bit_get(cmask, q) && aa > cm.best) {
+                        cm.best = aa;
+                        cm.idx = q;
+                        cm.val = a[k];
+                    }
+                }
+            }
+        }
+        // next column pivot, |u_r|^2, |v_r|^2 and (term p's products being
+        // complete) the cross sum of term p, in one reduction; the rows of
+        // the deferred products are read before its closing barrier so
+        // that no wave clears them for the next step while another reads
+        cm = wave_argmax_u(cm);
+        nu2 = wave_total(nu2);
+        nv2 = wave_total(nv2);
+        if constexpr (NW > 1) {
+            if (lane == 0) {
+                sh.abest[w] = cm.best;
+                sh.aidx[w] = cm.idx;
+                sh.aval[w] = cm.val;
+                sh.dsum[0][w] = nu2;
+                sh.dsum[1][w] = nv2;
+            }
+            __syncthreads();
+            cm = Arg<T>{sh.abest[0], sh.aidx[0], sh.aval[0]};
+            nu2 = sh.dsum[0][0];
+            nv2 = sh.dsum[1][0];
+#pragma unroll 4
+            for (int q = 1; q < NW; ++q) {
+                arg_combine(cm, Arg<T>{sh.abest[q], sh.aidx[q], sh.aval[q]});
+                nu2 += sh.dsum[0][q];
+                nv2 += sh.dsum[1][q];
+            }
+        }
+        double cross_p = 0.0;
+        if (pending) {
+            for (int l = 0; l < p; ++l) {
+                double gu = accu[0][l], gv = accv[0][l];
+#pragma unroll 4
+                for (int q = 1; q < NW; ++q) {
+                    gu += accu[q][l];
+                    gv += accv[q][l];
+                }
+                cross_p += gu * gv;
+            }
+        }
+        if constexpr (NW > 1) __syncthreads();
+        // ---- step 4: the norm recursion and the stopping test ----
+        ++r;
+        if (!fuse) {
+            double cross = 0.0;
+            if (!fixed) {
+                column_products<T, NT, DC>(Vread, nc, r - 1, sh.gv, sh);
+                for (int l = 0; l < r - 1; ++l) cross += sh.gu[l] * sh.gv[l];
+            }
+            S2 += 2.0 * cross + nu2 * nv2;
+            last_p = nu2 * nv2;
+            if (!fixed && !one_shot && sqrt(last_p) <= tol * sqrt(S2)) break;
+        } else {
+            if (pending) {
+                // term r - 2 = p, its products summed over the waves in order
+                S2 += 2.0 * cross_p + nu2p * nv2p;
+                last_p = nu2p * nv2p;
+                if (sqrt(last_p) <= tol * sqrt(S2)) {
+                    r -= 1;  // the speculative term is dropped
+                    break;
+                }
+            }
+            if (r == 1) {  // the first term has no products
+                S2 = nu2 * nv2;
+                last_p = S2;
+                pending = false;
+                if (sqrt(last_p) <= tol * sqrt(S2)) break;
+            } else {
+                pending = true;
+                nu2p = nu2;
+                nv2p = nv2;
+            }
+        }
+        // ---- step 6: next column pivot ----
+        if (cm.idx == INT_MAX) break;
+        j = cm.idx;
+    }
+    if (tid == 0) {
+        rank_out[b] = refused ? -1 : r;
+        if (steps_out) steps_out[b] = steps;
     }
 }
 
@@ -1582,15 +1627,16 @@ __global__ __launch_bounds__(NW * kWave) void aca_lds_kernel(
 // arguments of a class's launch from its first entry of the order
 template <typename T, int NT, int KR>
 void launch_class(const AcaArgs& a, int64_t o0, int64_t nb, int lds_words, hipStream_t st) {
-    if (nb <= 0) return;
-    const unsigned grid = (unsigned)(nb < 0x7fffffff ? nb : 0x7fffffff);
     KernelEval<T> K(a.kern);
-    hipLaunchKernelGGL((aca_kernel<T, NT, KR>), dim3(grid), dim3(NT),
-                       (size_t)lds_words * sizeof(uint32_t), st, (const T*)a.soa, a.soa64, a.n,
-                       a.d, K, a.blocks, a.order + o0, nb, a.uoff, a.voff, a.ubase, a.vbase,
-                       a.kmax, a.eps, a.aca_eta, (T)a.eps0, a.fixed, a.rtarget, a.one_shot,
-                       a.cap_only, Overflow{a.ovf_used, a.ovf_cap, a.ovf_u0, a.ovf_v0, a.ovf_moved},
-                       lds_words, (T*)a.U, (T*)a.V, a.rank, a.steps);
+    constexpr int64_t kGrid = 0x7fffffff;  // a workgroup per block
+    for (; nb > 0; nb -= kGrid, o0 += kGrid)
+        hipLaunchKernelGGL((aca_kernel<T, NT, KR>), dim3((unsigned)std::min(nb, kGrid)), dim3(NT),
+                           (size_t)lds_words * sizeof(uint32_t), st, (const T*)a.soa, a.soa64,
+                           a.n, a.d, K, a.blocks, a.order + o0, std::min(nb, kGrid), a.uoff,
+                           a.voff, a.ubase, a.vbase, a.kmax, a.eps, a.aca_eta, (T)a.eps0, a.fixed,
+                           a.rtarget, a.one_shot, a.cap_only,
+                           Overflow{a.ovf_used, a.ovf_cap, a.ovf_u0, a.ovf_v0, a.ovf_moved},
+                           lds_words, (T*)a.U, (T*)a.V, a.rank, a.steps);
 }
 
 template <typename T, int NW, int K, int NL>

@@ -49,9 +49,11 @@ def kernels(tmp_path_factory):
     return dict(zip(names, out.values()))
 
 
-@pytest.mark.parametrize("kernel", ["p1_tile_kernel", "rowtile_kernel"])
+@pytest.mark.parametrize("kernel", ["p1_tile_kernel", "rowtile_kernel", "aca_kernel",
+                                    "aca_lds_kernel", ""])
 def test_no_private_memory(kernels, kernel):
-    found = {k: v for k, v in kernels.items() if kernel + "<" in k or kernel + "(" in k}
+    """By family, and ("") every kernel of the library."""
+    found = {k: v for k, v in kernels.items() if kernel in k}
     assert found
     bad = {k: v for k, v in found.items() if v}
     assert not bad
