@@ -114,16 +114,37 @@ static int reuse(const char* name) {
 }
 
 // another allocator of the process takes memory: the next large block that comes
-// back makes room, and what is missing comes from the smallest block that covers it
+// back makes room, the block idle for longest first
 static int others(const char* name) {
     Card k;
     Cache c(Fake{&k});
     Block a = take(c, 100 * GB), b = take(c, 10 * GB), d = take(c, 20 * GB);
-    c.free(a.p, a.n);
     c.free(b.p, b.n);
+    c.free(a.p, a.n);
     k.free_[0] -= 155 * GB;  // 3 GB left
     c.free(d.p, d.n);
-    EXPECT(k.free_[0] == 13 * GB && c.cached() == 120 * GB);
+    EXPECT(k.free_[0] == 13 * GB && c.cached() == 120 * GB && k.held.count(b.p) == 0);
+    return 0;
+}
+
+// a program that moves on to other sizes on a card full of idle blocks: after its first
+// pass it keeps its own blocks and maps nothing more
+static int moves_on(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    std::vector<Block> v;
+    for (size_t n : {45, 45, 45, 60, 30, 20, 15, 10, 8, 5}) v.push_back(take(c, n * GB));
+    for (auto& b : v) c.free(b.p, b.n);
+    int m = 0;
+    for (int pass = 0; pass < 6; ++pass) {
+        Block s = take(c, 115 * GB), f = take(c, 12 * GB), u = take(c, 13 * GB), w = take(c, 25 * GB);
+        c.free(f.p, f.n);
+        c.free(s.p, s.n);
+        Block x = take(c, 33 * GB);
+        for (Block* b : {&u, &w, &x}) c.free(b->p, b->n);
+        if (pass == 1) m = k.mallocs;
+    }
+    EXPECT(k.mallocs == m);
     return 0;
 }
 
@@ -199,6 +220,7 @@ int main(int argc, char** argv) {
     if (n == "sequence") return sequence(argv[1]);
     if (n == "reuse") return reuse(argv[1]);
     if (n == "others") return others(argv[1]);
+    if (n == "moves_on") return moves_on(argv[1]);
     if (n == "too_large") return too_large(argv[1]);
     if (n == "devices") return devices(argv[1]);
     if (n == "foreign") return foreign(argv[1]);
@@ -218,7 +240,7 @@ def program(tmp_path_factory):
     return str(d / "t")
 
 
-@pytest.mark.parametrize("case", ["sequence", "reuse", "others", "too_large", "devices", "foreign",
+@pytest.mark.parametrize("case", ["sequence", "reuse", "others", "too_large", "devices", "foreign", "moves_on",
                                   "sort_space"])
 def test_block_cache(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True)
