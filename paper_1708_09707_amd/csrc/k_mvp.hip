@@ -20,6 +20,7 @@
 // alpha, beta, sigma2.  Each z row is written by one workgroup and every sum
 // has a fixed order, so the product is deterministic.
 #include "hmx_internal.h"
+#include "rowtile_lanes.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -856,49 +857,9 @@ __global__ __launch_bounds__(kTileThreads) void rowtile_kernel(
 
 // tile shapes of the row-tile kernel, (lanes per row group L, row vectors per
 // lane RV) = (16, 1), (32, 1), (64, 1), (64, 2), (64, 4), (8, 1) (the last for
-// tiles of at most 8 row vectors, whose columns would leave lanes of wider
-// groups without rows); the grid is one workgroup per tile, a fixed
-// persistent grid looping over the tiles, or one workgroup per row pass
-
-// Lanes per row group of the default row passes: tiles of need 16-byte lane units
-// a column (unit: bytes of R rows), full: the widest pass where the chip is full.
-//
-// A column that is whole cache lines splits into passes for nothing, so passes
-// are `full` wide (512 bytes; 256 in BF16) and half of it where that makes no
-// more than 4096 workgroups, and 128 bytes for the fewest tiles.  Columns of other
-// lengths share a line between two passes and leave part of the last one idle:
-// there one pass takes the whole column, and narrower ones only where they bring
-// idle compute units in.  Row-tile times in us by lanes 8/16/32/64 (FP64 before:
-// 64 for tiles past 64 rows; FP32 32; BF16 16):
-//   whole lines  FP64 N = 4096, 64 rows (64 tiles)       17 /  22 /  33 /  42
-//                     N = 2^14, 128 rows (128)           126 / 120 / 124 / 185
-//                     N = 2^17, 256 rows (512)          1861 /1601 /1664 /1973
-//                     N = 2^19, 256 rows (2048)         7854 /6774 /6223 /6833
-//                FP32 N = 2^16, 256 rows (256)           451 / 432 / 552 / 591
-//                     N = 2^20, 256 rows (4096)         9058 /7792 /7454 /7942
-//                BF16 N = 2^20, 64 rows (16384)         5888 /6299 /9553
-//                     N = 2^19, 256 rows (2048)         1637 /1723 /1946 /2265
-//                     N = 2^20, 256 rows (4096)         3871 /3578 /3868 /4316
-//   other        FP64 200003, 98 rows (2048)            2158 /1781 /1654 /1441
-//                     300007, 147 rows (2048)           4278 /3289 /2979 /3552
-//                     10000, 157 rows (64)                97 /  84 / 103 / 159
-//                FP32 150000, 147 rows (1024)           1138 / 979 /1054 / 867
-//                BF16 150000, 147 rows (1024)           2336 /2092 /1620 /2231
-//                     9000, 71 rows (128)                 45 /  56 /  97
-int rowtile_lanes(int64_t ntiles, int need, int unit, int full) {
-    auto works = [&](int L) { return ntiles * ((need + L - 1) / L); };
-    int L = 8;
-    while (L < need && L < 64) L *= 2;
-    if ((int64_t)need * unit % 128 == 0) {
-        L = std::min(L, full);
-        if (L == full && works(L) <= 4096) L /= 2;
-    } else {
-        if (need > 64) L = 32;
-        while (L > 16 && works(L) < 256) L /= 2;
-    }
-    if (L == 16 && works(L) <= 128) L = 8;
-    return L;
-}
+// few tiles, and for tiles of at most 8 row vectors, whose columns would leave
+// lanes of wider groups without rows); the grid is one workgroup per tile, a
+// fixed persistent grid looping over the tiles, or one workgroup per row pass
 
 template <typename SU, typename SN, typename T>
 hipError_t rowtile_dispatch(int64_t ntiles, const int32_t* tile_lo, const int64_t* meta,
@@ -915,13 +876,12 @@ hipError_t rowtile_dispatch(int64_t ntiles, const int32_t* tile_lo, const int64_
         if (config == kRowtileTall || !std::is_same<SU, SN>::value) {
             // one workgroup per row pass of 128 rows (64 lanes in FP64, 32 in
             // FP32, 16 in BF16), narrower when the largest tile is shorter
-            L = 16;
-            while (L < need && L * R < 128 && L < 64) L *= 2;
+            L = rowtile_lanes_tall(need, R);
         } else {
             // One workgroup per row pass; how many lanes of rows it takes
             // (rowtile_lanes) is by whether passes end on cache lines and by
             // how many workgroups there are
-            L = rowtile_lanes(ntiles, need, R * (int)sizeof(SU), sizeof(SU) == 2 ? 16 : 32);
+            L = rowtile_lanes(ntiles, need, (int)sizeof(SU));
         }
         shape = L == 8 ? 5 : (L == 16 ? 0 : (L == 32 ? 1 : 2));
         mode = 2;
