@@ -2257,9 +2257,10 @@ hipError_t matvec_launch(hmx_hmatrix_s* h, const void* x, void* z, double alpha,
 // A matvec without precomputed factors: the near field (and sigma2 x, beta z)
 // by the row tiles, then chunk by chunk the ACA of the chunk's blocks into
 // the column scratch, t = V^T x per block and z|tile += alpha U t per row
-// tile, then the ranks back to the leaves.  Synchronises st.
+// tile, then the ranks back to the leaves.  config: the row tiles' shape.
+// Synchronises st.
 void np_matvec(hmx_hmatrix_s* h, const void* x, void* z, double alpha, double beta,
-               hipStream_t st, hipEvent_t* ev) {
+               hipStream_t st, hipEvent_t* ev, int config) {
     const int f64 = h->f64;
     const size_t esz = h->esz;
     const int kmax = h->prm.max_rank;
@@ -2273,8 +2274,7 @@ void np_matvec(hmx_hmatrix_s* h, const void* x, void* z, double alpha, double be
     auto near = [&] {
         if (near_done) return;
         near_done = true;
-        check(matvec_launch(h, x, z, alpha, beta, st, nullptr, h->rt_config),
-              "matvec (near field)");
+        check(matvec_launch(h, x, z, alpha, beta, st, nullptr, config), "matvec (near field)");
     };
     if (ev || P.nl == 0) near();
     if (ev) check(hipEventRecord(ev[1], st), "event");
@@ -2400,7 +2400,7 @@ hmx_status matvec_call(hmx_hmatrix_s* h, const void* x, void* z, hmx_dtype vec_d
     if (h->far_np) {
         const Allocator ua{h->prm.dev_alloc, h->prm.dev_free, h->prm.alloc_ctx};
         AllocScope scope(&ua);
-        return guarded([&] { np_matvec(h, x, z, alpha, beta, (hipStream_t)stream, ev); });
+        return guarded([&] { np_matvec(h, x, z, alpha, beta, (hipStream_t)stream, ev, config); });
     }
     const hipError_t e = matvec_launch(h, x, z, alpha, beta, (hipStream_t)stream, ev, config);
     if (e != hipSuccess) {

@@ -18,11 +18,12 @@ inline int rowtile_lanes_tall(int need, int R) {
 //
 // A column that is whole cache lines splits into passes for nothing, so passes
 // are 512 bytes wide (256 in BF16) and half of that where it makes no more than
-// 4096 workgroups (in BF16 below 512 rows), and 128 bytes for the fewest tiles.  Columns of other lengths
-// share a line between two passes and leave part of the last one idle: there
-// one pass takes the whole column, and narrower ones only where they bring idle
-// compute units in (BF16: up to 1024 workgroups, at most 32 lanes).  One pass
-// takes FP64 columns of 33 to 63 units as well, where that fills the chip.
+// 4096 workgroups (in BF16 below 512 rows), and 128 bytes for the fewest tiles.
+// Columns of other lengths share a line between two passes and leave part of
+// the last one idle: there one pass takes the whole column, and narrower ones
+// only where they bring idle compute units in (BF16: up to 1024 workgroups, at
+// most 32 lanes).  One pass takes FP64 columns of 33 to 63 units as well, where
+// that fills the chip.
 // Row-tile times in us by lanes 8/16/32/64 (the tall passes above: FP64 64
 // lanes past 64 rows, else 32; FP32 32; BF16 16):
 //   whole lines  FP64 N = 4096, 64 rows (64 tiles)       17 /  22 /  33 /  42

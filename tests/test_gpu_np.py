@@ -219,3 +219,23 @@ def test_np_cg_and_unsupported(H):
         assert ei.value.status == H.HMX_ERR_UNSUPPORTED
     hs.close()
     hn.close()
+
+
+@pytest.mark.parametrize("far_recompute", [0, 1])
+def test_cg_keeps_one_shape(H, far_recompute):
+    """CG's products keep the order of sums of the 128-row passes, also without
+    precomputation: the default equals the solve with that shape set (FP64
+    64-row tiles: 32 lanes, a workgroup per pass), while a product by itself may
+    take another."""
+    n = 4096
+    pts = synth.uniform_points(n, 2, 41)
+    b = _dev(synth.normal_vector(n, 42))
+    print("CG N=%d F64 far_recompute=%d" % (n, far_recompute), flush=True)
+    hm = H.HMatrix(_dev(pts), "matern32", 0.1, compute_dtype="f64", leaf_size=64, eta=1.5,
+                   aca_eps=1e-8, max_rank=64, sigma2=1e-2, far_recompute=far_recompute)
+    x = [torch.zeros_like(b) for _ in range(2)]
+    for k, config in enumerate((-1, 11)):
+        H.hmx_set_tile_config(hm.h, config)
+        H.hmx_cg_solve(hm.h, b, x[k], rel_tol=1e-12, max_iter=15, raise_on_fail=False)
+    assert torch.equal(x[0], x[1])
+    hm.close()
