@@ -1611,6 +1611,8 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
                             h->tile_of_point.as<int32_t>(), cnt.as<int64_t>() + h->n_adm, st),
               "extent");
         h->npieces = scan(cnt.as<int64_t>(), nb);
+        // (the factors' pieces come first)
+        const int64_t nadm_pieces = h->n_adm > 0 ? read_scalar(cnt.as<int64_t>() + h->n_adm, st) : 0;
         alloc(unsorted, h->npieces * sizeof(Piece), "pieces");
         alloc(keys, h->npieces * 8, "piece keys");
         alloc(vals, h->npieces * 4, "piece vals");
@@ -1681,8 +1683,8 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
         check(launch_piece_data(h->pieces.as<Piece>(), h->npieces, h->tile_lo.as<int32_t>(),
                                 h->adm.as<int4>(), h->dense.as<int4>(), rfo.as<int64_t>(), F.p,
                                 f64 ? h->soa64.p : h->soa32.p, n, d,
-                                kernel_fn(h->kern, h->kd), h->upool.p, nullptr, smode, h->nmode, false,
-                                h->upool_entries, st),
+                                kernel_fn(h->kern, h->kd), h->upool.p, nullptr, smode, h->nmode,
+                                false, h->upool_entries, nadm_pieces, st),
               "piece data (factors)");
         h->Ru = R;
         // ---- phase-1 sources (t = V^T x by row tiles) ----
@@ -1690,7 +1692,6 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
         // leaf, or (symmetric far field) for the leaves that are their own
         // mirror; the other leaves read their mirror's factor pieces
         const int32_t* prt = h->sym ? h->partner.as<int32_t>() : nullptr;
-        const int64_t nadm_pieces = h->n_adm > 0 ? read_scalar(cnt.as<int64_t>() + h->n_adm, st) : 0;
         const int64_t pfc_u = h->sym ? nadm_pieces : 0;  // pfc entries of the factor pieces
         DevBuf cntv;
         alloc(cntv, (h->n_adm + 1) * 8, "V piece counts");
@@ -1783,7 +1784,7 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
                                     h->adm.as<int4>(), h->dense.as<int4>(), nullptr, nullptr,
                                     f64 ? h->soa64.p : h->soa32.p, n, d,
                                     kernel_fn(h->kern, h->kd), h->upool.p, h->npool.p, smode,
-                                    h->nmode, true, h->npool_entries, st),
+                                    h->nmode, true, h->npool_entries, h->npieces - nadm_pieces, st),
                   "piece data (near field)");
         check(hipStreamSynchronize(st), "near-field sync");
     }

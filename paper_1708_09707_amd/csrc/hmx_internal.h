@@ -491,7 +491,8 @@ hipError_t launch_piece_data(const Piece* pieces, int64_t np, const int32_t* til
                              int d, KernelFn kern,
                              void* upool, void* npool, int fmode, int nmode,
                              bool near /*the near-field pieces, else the factors'*/,
-                             int64_t entries /*of the pool(s) filled*/, hipStream_t st);
+                             int64_t entries /*of the pool filled*/,
+                             int64_t kind_pieces /*of that kind*/, hipStream_t st);
 // workgroups of the sums over all leaves: one atomic per wave on one word, so the
 // waves are bounded (894342 leaves: 328 us with a thread per leaf, now 28)
 constexpr int kStatBlocks = 256;

@@ -391,10 +391,10 @@ __device__ __forceinline__ void near_dispatch(const KernelEval<T>& K, const T* _
 // stores; rows past the tile's end are zero.  A factor piece copies rows row0 ..
 // of its U columns (NEAR false), a near-field piece evaluates phi (true; one
 // kernel for both holds the registers of either).  Small pieces are bound by the
-// latency of piece, block, offset and entry in turn, so by the pieces in flight.
-// N = 200003 3-d BF16 (49-row tiles, 2.9 GB of near field, 1.8 GB each of U and V):
-// U 3.0 ms as a workgroup per piece and two bytes a load, now 1.25; near field
-// 3.25, now 1.57; V (vpiece_data_kernel) 2.4, now 1.5.  N = 2^20 2-d FP32
+// latency of piece, block, offset and entry in turn, so by the pieces in flight
+// (piece_by_wave has the times of both).  N = 200003 3-d BF16 (49-row tiles, 2.9 GB
+// of near field, 1.8 GB each of U and V): as workgroups with two bytes a load
+// U 3.0 ms, V 2.4, near field 3.25, now 1.25, 1.5 and 1.57.  N = 2^20 2-d FP32
 // (256-row tiles): U 2.9 and 2.8 ms, V 3.6 and 2.8, near field 7.1 ms as before.
 template <typename SU, typename SN, typename T, int R, int TPP, bool NEAR>
 __global__ __launch_bounds__(256) void piece_data_kernel(
@@ -575,7 +575,6 @@ __global__ void chunk_bounds_kernel(const int64_t* __restrict__ cap_off, int64_t
 // partial row sets are summed in LDS in a fixed order and the tile is
 // scattered to the original order.
 constexpr int kTileThreads = 256;
-constexpr int kWaveUnits = 512;
 constexpr int kChunk = 2048;
 constexpr int kUnroll = 16;
 constexpr int kEvalUnroll = 4;  // near-field columns evaluated per iteration (recompute mode)
@@ -987,13 +986,9 @@ hipError_t launch_piece_data(const Piece* pieces, int64_t np, const int32_t* til
                              const int4* adm, const int4* dense, const int64_t* uoff,
                              const void* Usrc, const void* soa, int64_t n, int d, KernelFn kern,
                              void* upool, void* npool, int fmode, int nmode, bool near,
-                             int64_t entries, hipStream_t st) {
-    if (np == 0 || (near && nmode == 3)) return hipSuccess;
-    // a wave per piece up to kWaveUnits 16-byte units a piece on average: with 49-row
-    // BF16 tiles (some 60 and 340 units, factor and near-field) 1.25 against 3.0 ms
-    // and 1.57 against 3.25; a near-field piece of 256 x 256 FP32 has 16384
-    // units, which a wave would take one after another
-    const bool wave = entries / np <= (int64_t)kWaveUnits * rows_per_unit(fmode, nmode);
+                             int64_t entries, int64_t kind_pieces, hipStream_t st) {
+    if (np == 0 || kind_pieces == 0 || (near && nmode == 3)) return hipSuccess;
+    const bool wave = piece_by_wave(near, entries / rows_per_unit(fmode, nmode), kind_pieces);
     const unsigned grid = grid_cap(wave ? (np + 3) / 4 : np, 1 << 20);
 // each combination's unit (rows_per_unit) is a template argument
 #define HMX_PD(SU, SN, T, R)                                                                  \
@@ -1039,7 +1034,7 @@ hipError_t launch_vpiece_data(const Piece* pieces, int64_t np, const int32_t* ti
                               const int4* adm, const int64_t* vfo, const void* src, void* pool,
                               int smode, int64_t entries, hipStream_t st) {
     if (np == 0) return hipSuccess;
-    const bool wave = entries / np <= (int64_t)kWaveUnits * rows_per_unit(smode, smode);
+    const bool wave = piece_by_wave(false, entries / rows_per_unit(smode, smode), np);
     const unsigned grid = grid_cap(wave ? (np + 3) / 4 : np, 1 << 20);
 #define HMX_VP(S)                                                                             \
     if (wave)                                                                                 \

@@ -1,5 +1,5 @@
-// The shape of the default row passes of the stored product's row tiles, by
-// sizes alone (host code, no HIP types).
+// Rules by sizes alone for the row tiles' pieces and passes (host code, no HIP
+// types).
 #pragma once
 #include <cstdint>
 
@@ -70,6 +70,25 @@ inline int rowtile_lanes(int64_t ntiles, int need, int es) {
     while (L > 16 && works(L) < (bf16 ? 1024 : 256)) L /= 2;
     if (L == 16 && works(L) < (bf16 ? 129 : 128)) L = 8;
     return L;
+}
+
+// Whether a wave fills a piece of a matrix pool (else a workgroup of four): units
+// 16-byte units over `pieces` pieces of that kind.  Small pieces are bound by the
+// latency of piece, block and offset in turn, so by the pieces in flight; in large
+// ones a wave takes the units one after another.  us as a workgroup / a wave:
+//   near field  N = 200003 3-d BF16, 49 x 49 (343 units a piece)  3115 / 1240
+//               100003 3-d FP32, 49 x 49 (637)                    1180 /  607
+//               200000 2-d FP64, 49 x 49 (1225)                   1448 /  976
+//               200000 2-d FP32, 98 x 98 (2450)                    628 /  463
+//               60000 3-d FP32, 117 x 117 (3510)                   581 /  659
+//               60000 3-d BF16, 235 x 235 (7050)                   490 /  531
+//               200000 2-d FP64, 196 x 196 (19200)                2831 / 3736
+//               4096 2-d FP64, 64 x 64 (2048, 1500 pieces)          20 /   28
+//   factors     200003 3-d BF16, 49 rows (below 512)              2397 / 1620
+//               200000 2-d FP64, 49 rows (below 512)              1405 / 1107
+//               200000 2-d FP64, 196 rows (1024 to 2048)           795 /  943
+inline bool piece_by_wave(bool near, int64_t units, int64_t pieces) {
+    return pieces >= (near ? 8192 : 1) && units / pieces <= (near ? 3072 : 512);
 }
 
 }  // namespace hmx

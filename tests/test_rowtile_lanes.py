@@ -1,6 +1,7 @@
-"""The rule that picks the lanes of the stored product's row passes, over measured
-row tiles (MI355X): the pick is never more than 3% slower than the passes of
-128 rows, nor 20% slower than the fastest shape.  CPU only."""
+"""The rules by size of the row tiles, over measured tiles and pieces (MI355X).
+Lanes of the stored product's row passes: never more than 3% slower than the
+passes of 128 rows, nor 20% slower than the fastest shape.  Threads of a matrix
+pool's piece: the faster of a wave and a workgroup.  CPU only."""
 import os
 import subprocess
 
@@ -34,7 +35,11 @@ def pick(tmp_path_factory):
 #include <cstdio>
 #include <cstdlib>
 #include "rowtile_lanes.h"
-int main(int, char** a) {
+int main(int n, char** a) {
+    if (n == 4 && atoi(a[1]) < 2) {
+        printf("%d\\n", (int)hmx::piece_by_wave(atoi(a[1]), atol(a[2]), atol(a[3])));
+        return 0;
+    }
     const int es = atoi(a[1]), R = 16 / es, need = (atoi(a[3]) + R - 1) / R;
     printf("%d %d\\n", hmx::rowtile_lanes(atol(a[2]), need, es), hmx::rowtile_lanes_tall(need, R));
 }
@@ -58,3 +63,16 @@ def test_pick_is_a_shape(pick, es):
     for tiles in (1, 31, 256, 5000, 1 << 20):
         for rows in (1, 2, 63, 64, 65, 1000, 100000):
             assert set(pick(es, tiles, rows)) <= {8, 16, 32, 64}
+
+
+# near field, units a piece (of factors: a bound), pieces, us as a workgroup and as a wave
+PIECES = [(1, 343, 1000000, 3115, 1240), (1, 637, 500000, 1180, 607), (1, 1225, 100000, 1448, 976),
+          (1, 2450, 50000, 628, 463), (1, 3510, 60000, 581, 659), (1, 7050, 20000, 490, 531),
+          (1, 19200, 30000, 2831, 3736), (1, 2048, 1500, 20, 28), (0, 511, 4000000, 2397, 1620),
+          (0, 511, 900000, 1405, 1107), (0, 1024, 100000, 795, 943)]
+
+
+@pytest.mark.parametrize("near,units,pieces,group,wave", PIECES)
+def test_piece_threads(pick, near, units, pieces, group, wave):
+    (by_wave,) = pick(near, units * pieces, pieces)
+    assert by_wave == (wave < group)
