@@ -48,10 +48,13 @@ struct MlpTile {
     float dout[kMT];
 };
 
-// out row i = relu(bias_i + sum_k W[i, k] in row k), eight rows a wave
+// out row i = relu(bias_i + sum_k W[i, k] in row k), eight rows a wave; zero for a
+// lane that has no sample (live false): what the biases make of no input may be
+// infinite, and infinity times its zero delta is no zero
 template <int IN>
 __device__ __forceinline__ void tile_layer(const float* __restrict__ W, const float* __restrict__ bias,
-                                           const float* in, float* out, int wave, int lane) {
+                                           const float* in, float* out, int wave, int lane,
+                                           bool live) {
     const int i0 = wave * 8;
     float s[8];
 #pragma unroll
@@ -63,7 +66,7 @@ __device__ __forceinline__ void tile_layer(const float* __restrict__ W, const fl
         for (int u = 0; u < 8; ++u) s[u] = __builtin_fmaf(W[(i0 + u) * IN + k], x, s[u]);
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) out[(i0 + u) * kMP + lane] = s[u] > 0.f ? s[u] : 0.f;
+    for (int u = 0; u < 8; ++u) out[(i0 + u) * kMP + lane] = live && s[u] > 0.f ? s[u] : 0.f;
 }
 
 // dp row k = [a row k > 0] sum_j W[j, k] d row j: wave w forms rows 16 (w / 2)
@@ -133,17 +136,18 @@ __global__ __launch_bounds__(kMW * 64) void mlp_tile_kernel(
     double lsum = 0.0;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int64_t s0 = t * kMT;
+        const bool live = !GRAD || s0 + lane < B;
         {
             const int b = tid >> 3, k = tid & 7;
             const int64_t sb = s0 + b;
             T.x[k * kMP + b] = sb < B ? (X[sb * kIn + k] - mean[k]) * scale[k] : 0.f;
         }
         __syncthreads();
-        tile_layer<kIn>(w + kOffW1, w + kOffB1, T.x, T.a1, wave, lane);
+        tile_layer<kIn>(w + kOffW1, w + kOffB1, T.x, T.a1, wave, lane, live);
         __syncthreads();
-        tile_layer<kH>(w + kOffW2, w + kOffB2, T.a1, T.a2, wave, lane);
+        tile_layer<kH>(w + kOffW2, w + kOffB2, T.a1, T.a2, wave, lane, live);
         __syncthreads();
-        tile_layer<kH>(w + kOffW3, w + kOffB3, T.a2, T.a3, wave, lane);
+        tile_layer<kH>(w + kOffW3, w + kOffB3, T.a2, T.a3, wave, lane, live);
         __syncthreads();
         if (wave == 0) {
             float o = w[kOffB4];
@@ -356,7 +360,7 @@ __global__ void features_kernel(const int4* __restrict__ blocks, const int2* __r
 // standardisation, the four layers with the weights staged in LDS (every lane
 // reads the same weight at the same time, so LDS broadcasts), and the ACA
 // target clamp(ceil(pred) + 1, 1, min(kmax, m, n)).  The sums run in the same
-// order as in the layer kernels.
+// order as in mlp_tile_kernel.
 constexpr int kInferThreads = 256;
 
 __global__ __launch_bounds__(kInferThreads) void rank_predict_kernel(

@@ -430,3 +430,30 @@ def test_tiles_match_oracle(H, orc, B):
     assert abs(loss - loss_o) <= 1e-5 * abs(loss_o) + 1e-7
     assert _rel(g.cpu().numpy().astype(np.float64), g_o) <= 1e-4
     mlp.close()
+
+
+@pytest.mark.parametrize("B", [1, 65, 200])
+def test_tile_padding_stays_out_of_the_gradient(H, orc, B):
+    """Biases and weights that cancel on every sample and overflow where there is
+    none: the last tile's empty places must not reach the gradient (infinity
+    times zero), which is finite and the oracle's."""
+    g = synth.rng(77)
+    w = synth.mlp_init_params(31)
+    W1, b1 = w[:512].reshape(64, 8), w[512:576]
+    W1[:, 0] = 2e38  # feature 0 is -1 on every sample: bias and product cancel
+    b1[:] = 2e38
+    w[576:576 + 4096] = np.abs(w[576:576 + 4096]) + 1.0  # an uncancelled row overflows
+    w[4672:4736] = w[8832:8896] = 0.1  # biases of the second and third layers
+    X = np.zeros((B, 8), np.float32)
+    X[:, 0] = -1.0
+    y = g.integers(1, 40, B).astype(np.float32)
+    mlp = H.RankMLP(w)
+    mlp.set_params(w, np.zeros(8, np.float32), np.ones(8, np.float32))
+    loss, grad = mlp.loss_grad(_dev(X), _dev(y), q=0.9)
+    loss_o, g_o = orc.mlp_loss_grad(w.astype(np.float64), X.astype(np.float64),
+                                    y.astype(np.float64), q=0.9)
+    grad = grad.cpu().numpy()
+    assert np.isfinite(grad).all()
+    assert abs(loss - loss_o) <= 1e-5 * abs(loss_o) + 1e-7
+    assert _rel(grad, g_o) <= 1e-4
+    mlp.close()
