@@ -457,3 +457,23 @@ def test_tile_padding_stays_out_of_the_gradient(H, orc, B):
     assert abs(loss - loss_o) <= 1e-5 * abs(loss_o) + 1e-7
     assert _rel(grad, g_o) <= 1e-4
     mlp.close()
+
+
+@pytest.mark.parametrize("B", [100, 64 * 256 + 1])
+def test_forward_into_its_own_features(H, B):
+    """An output that lies in the features' storage, at its start, in the middle,
+    at its end and across its ends: the same bits as one of its own."""
+    X, _ = _features_data(B, 91)
+    w = synth.mlp_init_params(23)
+    mlp = H.RankMLP(w)
+    mlp.set_params(w, X.mean(axis=0), (1.0 / X.std(axis=0).clip(1e-6)).astype(np.float32))
+    want = mlp.forward(_dev(X))
+    for at in (-(B // 2), 0, 3 * B + 1, 7 * B, 7 * B + B // 2):
+        room = torch.zeros(10 * B, dtype=torch.float32, device="cuda:0")
+        feat = room[B:9 * B].view(B, 8)
+        feat.copy_(_dev(X))
+        out = room[B + at:2 * B + at]
+        H.hmx_mlp_forward(mlp.handle, feat, out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    mlp.close()
