@@ -751,16 +751,16 @@ struct AcaPlan {
     const int32_t* rt = nullptr;         // learned targets, or null
 };
 
-// clusters of split_rows(h) or more points put their blocks on many
-// workgroups each, of kBigRows or more in the 512-thread class; clusters of
-// at most kTinyRows points in the single-wave class.  With the chunks
-// interleaving the levels, a block of up to 2^17 rows runs as well on one
-// 512-thread workgroup beside the other classes as on many workgroups; the
-// default keeps the many-workgroup path for blocks whose bitmasks would not
-// fit a workgroup's LDS
+// Clusters of split_rows(h) or more points put their blocks on many workgroups
+// each; below that a block has one workgroup, of a size class by its own points
+// (kAcaClassRows).  With the chunks interleaving the levels, a block of up to 2^17
+// rows runs as well on one workgroup beside the other classes as on many; the
+// default keeps the many-workgroup path for blocks whose bitmasks would not fit a
+// workgroup's LDS
 constexpr int64_t kDefaultSplitRows = (int64_t)1 << 18;
-// (kBigRows and kTinyRows group the leaves of a batched handle; the ACA's own
-// size classes are cut by the blocks' sizes, kAcaClassRows)
+// A batched handle lists its leaves in four groups of tree levels, the largest
+// clusters first (many workgroups, from kBigRows points, above kTinyRows, the
+// rest), so that the many-workgroup blocks of all problems are a prefix
 constexpr int64_t kBigRows = 4096;
 constexpr int64_t kTinyRows = 512;
 

@@ -72,19 +72,6 @@ __device__ __forceinline__ void arg_combine(Arg<T>& a, const Arg<T>& b) {
     if (b.best > a.best || (b.best == a.best && b.idx < a.idx)) a = b;
 }
 
-template <typename T>
-__device__ __forceinline__ Arg<T> wave_argmax(Arg<T> a) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        Arg<T> b;
-        b.best = __shfl_xor(a.best, o, 64);
-        b.idx = __shfl_xor(a.idx, o, 64);
-        b.val = __shfl_xor(a.val, o, 64);
-        arg_combine(a, b);
-    }
-    return a;
-}
-
 // ---------------------------------------------------------------------------
 // Wave reductions on the DPP crossbar: the quad swaps (lane i with i ^ 1, then
 // i ^ 2), the half-row mirror (i with 7 - i) and the row mirror (i with
@@ -298,38 +285,6 @@ struct Overflow {
     int64_t cap, u0, v0;
     int64_t* moved;  // per block of the launch: the offset granted, else left as is
 };
-
-template <typename T, int NW>
-__device__ Arg<T> block_argmax(Arg<T> a, AcaShared<T, NW>& sh) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    a = wave_argmax(a);
-    if (lane == 0) {
-        sh.abest[w] = a.best;
-        sh.aidx[w] = a.idx;
-        sh.aval[w] = a.val;
-    }
-    __syncthreads();
-    Arg<T> r{sh.abest[0], sh.aidx[0], sh.aval[0]};
-    for (int q = 1; q < NW; ++q) {
-        Arg<T> b{sh.abest[q], sh.aidx[q], sh.aval[q]};
-        arg_combine(r, b);
-    }
-    __syncthreads();
-    return r;
-}
-
-// sum of a double across the workgroup, same tree on every thread
-template <typename T, int NW>
-__device__ double block_sum(double a, AcaShared<T, NW>& sh, int slot) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    a = wave_sum(a);
-    if (lane == 0) sh.dsum[slot][w] = a;
-    __syncthreads();
-    double s = sh.dsum[slot][0];
-    for (int q = 1; q < NW; ++q) s += sh.dsum[slot][q];
-    __syncthreads();
-    return s;
-}
 
 // the smallest value of the wave, on every lane
 __device__ __forceinline__ int wave_min(int v) {
@@ -1123,9 +1078,9 @@ __global__ __launch_bounds__(NT, (aca_min_waves<T>())) void aca_kernel(
 
 // ---------------------------------------------------------------------------
 // Blocks of at most S = 64 NW K points a side: thread t holds rows and columns
-// t, t + NT, ... of the block (one pass), and the first nl columns of U and V
-// live in LDS beside the points' coordinates (later ones are read back from
-// memory).  A step then reads no memory but the columns past nl: a pivot's row
+// t, t + NT, ... of the block (one pass) with their points' coordinates in
+// registers, and the first nl columns of U and V live in LDS (later ones are
+// read back from memory).  A step then reads no memory but the columns past nl: a pivot's row
 // of U or column of V is one gather, a lane per column, whose values become
 // scalar operands of the updates.  The columns not yet computed hold zeros, so
 // they are taken in whole batches.  The products of a new term with the
@@ -1286,7 +1241,7 @@ __global__ __launch_bounds__(NW * kWave) void aca_lds_kernel(
                     sh.idx[0][w] = cand;
                 }
             }
-            __syncthreads();  // (publishes the LDS columns and coordinates as well)
+            __syncthreads();  // (publishes the zeroed LDS columns as well)
             if constexpr (NW > 1) {
                 double bk = sh.key[0][0];
                 cand = sh.idx[0][0];
