@@ -16,11 +16,14 @@
 // the queue (out of resources).  So whenever large blocks are kept, kReserve
 // bytes of the device are free: a miss gives idle blocks back until the request
 // and the reserve fit, and so does a large block that comes back while the
-// reserve is not free.  The one idle for longest goes first: a program that has
-// moved on to other sizes loses the blocks of the earlier ones and then keeps its
-// own (giving back the block that fits the shortage best took a build of N = 2^20
-// points from 63 ms to 3.8 s, its own scratch being unmapped in every pass while
-// the blocks of earlier handles stayed).
+// reserve is not free.  Blocks that the last kRecent allocations passed over go
+// first, the oldest before others (a program that has moved on to other sizes
+// loses the blocks of the earlier ones and keeps its own), then the smallest
+// that covers what is missing, else the largest.  Either rule alone has the
+// program map its own blocks anew in every pass: the best fit unmaps the pass's
+// scratch while the blocks of earlier handles stay (a build of N = 2^20 points
+// 3.8 s instead of 63 ms), the oldest first more than is missing, and what the
+// next step needs, once all blocks are of the running pass.
 //
 // Blocks enter the cache only after the work using them has completed (the
 // build synchronises its stream before releasing scratch, destroy
@@ -47,6 +50,9 @@ class BlockCache {
     // back (smaller ones do not move the reserve)
     static constexpr size_t kLarge = (size_t)64 << 20;
 
+    // a build makes about 100 allocations: blocks of the last three passes or so
+    static constexpr uint64_t kRecent = 300;
+
     explicit BlockCache(Driver d = Driver()) : drv_(d) {}
 
     static size_t round(size_t bytes) {
@@ -62,6 +68,7 @@ class BlockCache {
         *oom = false;
         {
             std::lock_guard<std::mutex> lk(mu_);
+            ++clock_;
             for (auto it = idle_.lower_bound(*bytes); it != idle_.end(); ++it) {
                 if (it->first / 4 * 3 > *bytes) break;
                 if (it->second.dev != dev) continue;
@@ -95,7 +102,7 @@ class BlockCache {
         const int dev = drv_.device();
         std::lock_guard<std::mutex> lk(mu_);
         if (owned_.count(p) == 0) return;
-        idle_.insert({bytes, Block{dev, p, ++clock_}});
+        idle_.insert({bytes, Block{dev, p, clock_}});
         cached_ += bytes;
         if (bytes >= kLarge) make_room(dev, kReserve);
     }
@@ -126,12 +133,12 @@ class BlockCache {
     struct Block {
         int dev;
         void* p;
-        uint64_t since;  // when it came back
+        uint64_t since;  // allocations made until it came back
     };
     using Idle = std::multimap<size_t, Block>;  // by size
 
-    // large idle blocks of dev back to the driver, the oldest first, until `want`
-    // bytes are free or none is left
+    // large idle blocks of dev back to the driver until `want` bytes are free or
+    // none is left
     void make_room(int dev, size_t want) {
         if (idle_.empty()) return;
         size_t fr = 0;
@@ -139,10 +146,17 @@ class BlockCache {
         bool any = false;
         while (fr < want) {
             auto pick = idle_.end();
-            for (auto it = idle_.lower_bound(kLarge); it != idle_.end(); ++it)
-                if (it->second.dev == dev &&
-                    (pick == idle_.end() || it->second.since < pick->second.since))
+            bool old = false, covers = false;
+            for (auto it = idle_.lower_bound(kLarge); it != idle_.end(); ++it) {  // by size
+                if (it->second.dev != dev) continue;
+                if (clock_ - it->second.since > kRecent) {
+                    if (!old || it->second.since < pick->second.since) pick = it;
+                    old = true;
+                } else if (!old && !covers) {
                     pick = it;
+                    covers = it->first >= want - fr;
+                }
+            }
             if (pick == idle_.end()) break;
             if (!any) drv_.sync();
             any = true;

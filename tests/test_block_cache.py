@@ -114,7 +114,7 @@ static int reuse(const char* name) {
 }
 
 // another allocator of the process takes memory: the next large block that comes
-// back makes room, the block idle for longest first
+// back makes room, by the smallest recent block that covers what is missing
 static int others(const char* name) {
     Card k;
     Cache c(Fake{&k});
@@ -124,6 +124,22 @@ static int others(const char* name) {
     k.free_[0] -= 155 * GB;  // 3 GB left
     c.free(d.p, d.n);
     EXPECT(k.free_[0] == 13 * GB && c.cached() == 120 * GB && k.held.count(b.p) == 0);
+    return 0;
+}
+
+// but first by a block that the program has passed over for hundreds of allocations
+static int old_first(const char* name) {
+    Card k;
+    Cache c(Fake{&k});
+    Block a = take(c, 100 * GB), d = take(c, 20 * GB);
+    c.free(a.p, a.n);
+    for (int i = 0; i < 400; ++i) {
+        c.free(d.p, d.n);
+        d = take(c, 20 * GB);
+    }
+    k.free_[0] = 3 * GB;
+    c.free(d.p, d.n);
+    EXPECT(k.free_[0] == 103 * GB && k.held.count(d.p) && !k.held.count(a.p));
     return 0;
 }
 
@@ -145,6 +161,60 @@ static int moves_on(const char* name) {
         if (pass == 1) m = k.mallocs;
     }
     EXPECT(k.mallocs == m);
+    return 0;
+}
+
+// builds of four kinds of handles, as allocated: scratch, factors, two pools, near
+// field, with sizes that vary from input to input; three inputs of the last kind in
+// turn map nothing more after the second round
+struct Handle { Block b[3]; };
+static Handle build(Cache& c, double scratch, double factors, double pool, double near) {
+    Block small[40];
+    for (auto& b : small) b = take(c, 1000);
+    for (auto& b : small) c.free(b.p, b.n);
+    auto sz = [](double g) { return (size_t)(g * (double)GB); };
+    Block s = take(c, sz(scratch)), f = take(c, sz(factors));
+    c.free(s.p, s.n);
+    Handle h;
+    h.b[0] = take(c, sz(pool));
+    h.b[1] = take(c, sz(pool));
+    c.free(f.p, f.n);
+    h.b[2] = take(c, sz(near));
+    return h;
+}
+static void close(Cache& c, Handle& h) { for (auto& b : h.b) c.free(b.p, b.n); }
+
+static int rounds(const char* name) {
+    for (unsigned seed = 1; seed <= 200; ++seed) {
+        Card k;
+        Cache c(Fake{&k});
+        unsigned r = seed * 2654435761u;
+        auto vary = [&] { r = r * 1664525u + 1013904223u; return 0.95 + 0.1 * (double)(r >> 8) / (1 << 24); };
+        const double kinds[4][4] = {{82, 14.5, 7.3, 34.5}, {21, 4.2, 2.1, 7.4}, {77, 15, 15, 25}, {12, 2.3, 1.2, 8}};
+        for (auto& d : kinds) {
+            std::vector<Handle> v;
+            for (int i = 0; i < 3; ++i) {
+                const double j = vary();
+                v.push_back(build(c, d[0] * j, d[1] * j, d[2] * j, d[3] * (0.8 + 0.2 * vary())));
+            }
+            for (int i = 0; i < 5; ++i) {
+                const double j = vary();
+                Handle h = build(c, d[0] * j, d[1] * j, d[2] * j, d[3] * (0.8 + 0.2 * vary()));
+                close(c, h);
+                if (i == 0) { close(c, v[2]); close(c, v[1]); }
+            }
+            close(c, v[0]);
+        }
+        double j[3] = {vary(), vary(), vary()}, n[3] = {vary(), vary(), vary()};
+        int m = 0;
+        for (int i = 0; i < 24; ++i) {
+            if (i == 6) m = k.mallocs;
+            Handle h = build(c, 92 * j[i % 3], 14.8 * j[i % 3], 7.4 * j[i % 3], 39 * (0.8 + 0.2 * n[i % 3]));
+            close(c, h);
+            EXPECT(reserved(k, c));
+        }
+        EXPECT(k.mallocs == m);
+    }
     return 0;
 }
 
@@ -220,7 +290,9 @@ int main(int argc, char** argv) {
     if (n == "sequence") return sequence(argv[1]);
     if (n == "reuse") return reuse(argv[1]);
     if (n == "others") return others(argv[1]);
+    if (n == "old_first") return old_first(argv[1]);
     if (n == "moves_on") return moves_on(argv[1]);
+    if (n == "rounds") return rounds(argv[1]);
     if (n == "too_large") return too_large(argv[1]);
     if (n == "devices") return devices(argv[1]);
     if (n == "foreign") return foreign(argv[1]);
@@ -240,8 +312,8 @@ def program(tmp_path_factory):
     return str(d / "t")
 
 
-@pytest.mark.parametrize("case", ["sequence", "reuse", "others", "too_large", "devices", "foreign", "moves_on",
-                                  "sort_space"])
+@pytest.mark.parametrize("case", ["sequence", "reuse", "others", "too_large", "devices", "foreign",
+                                  "old_first", "moves_on", "rounds", "sort_space"])
 def test_block_cache(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
