@@ -385,7 +385,7 @@ __device__ void block_sum_cols(double* acc, int nk, double* out, AcaShared<T, NW
 
 // first column: the sigma point nearest to the centre 0.5 (a + b) of tau's
 // bounding box, squared distance summed in dimension order, all in FP64
-// without contraction
+// without contraction (the first point where every distance overflows)
 template <typename T, int NT>
 __device__ int first_column(const double* __restrict__ soa64, int64_t n, int d, int4 bl,
                             AcaShared<T, NT / kWave>& sh) {
@@ -419,7 +419,8 @@ __device__ int first_column(const double* __restrict__ soa64, int64_t n, int d, 
             bi = q;
         }
     }
-    return block_argmin_f64(best, bi, sh);
+    bi = block_argmin_f64(best, bi, sh);
+    return bi == INT_MAX ? 0 : bi;
 }
 
 __device__ __forceinline__ bool bit_get(const uint32_t* m, int i) {
@@ -1252,6 +1253,7 @@ __global__ __launch_bounds__(NW * kWave) void aca_lds_kernel(
                     }
                 __syncthreads();
             }
+            cand = cand == INT_MAX ? 0 : cand;
             j = __builtin_amdgcn_readfirstlane(cand);
         }
         T p[3];  // the pivot's point

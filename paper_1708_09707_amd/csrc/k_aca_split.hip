@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kST) void split_init_kernel(SplitArgs a, int64_t nb
         R = nc < R ? nc : R;
         SplitState s{};
         s.R = R;
-        s.j = j;
+        s.j = j == INT_MAX ? 0 : j;  // (every distance overflows: the first point)
         const bool sized = a.rtarget && a.rtarget[b] > 0;
         s.one_shot = sized && a.one_shot;
         s.target = sized ? (a.rtarget[b] < R ? a.rtarget[b] : R) : R;

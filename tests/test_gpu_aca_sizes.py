@@ -107,3 +107,23 @@ def test_single_block_many_columns(H, orc, m, n):
     print("  rank %d, vs dense %.1e" % (r, _rel(z, zd)), flush=True)
     assert r > 64
     assert _rel(z, zd) <= 1e-10
+
+
+@pytest.mark.parametrize("split_rows", [0, 1500])
+@pytest.mark.parametrize("near_recompute", [0, 1])
+def test_distances_that_overflow(H, near_recompute, split_rows):
+    """Coordinates of 1e200: every squared distance is infinite, so no point is
+    nearest to a box's centre and the first is taken (as the oracle does); the
+    kernel matrix is the identity, and every low-rank block is zero.  All size
+    classes, and the many-workgroup path."""
+    n = 20000
+    pts = synth.uniform_points(n, 2, 71) * 1e200
+    x = _dev(synth.normal_vector(n, 72))
+    print("N %d, coordinates to 1e200, split rows %d" % (n, split_rows), flush=True)
+    hm = H.HMatrix(_dev(pts), "gaussian", 1.0, compute_dtype="f64", leaf_size=32, eta=1.5,
+                   aca_eps=1e-6, max_rank=16, near_recompute=near_recompute,
+                   aca_split_rows=split_rows)
+    assert hm.stats().n_adm > 0
+    assert torch.equal(hm.matvec(x), x)
+    assert not hm.ranks().any()
+    hm.close()
