@@ -13,8 +13,8 @@
 // reductions are most of the work) and by the latency of the columns' loads in
 // the large ones.  The start of this form (256-row passes of one wave, every
 // product a reduction of its own, columns in memory) spent 10200 vector
-// instructions on an average one-wave block of N = 2 10^5, d = 3; the classes
-// that replace it 3400 to 8000 by size.  ACA phase before and after: N = 200003
+// instructions on an average one-wave block of N = 2 10^5, d = 3; the one-wave
+// classes that replace it 3443, 5728 and 8872 (to 64, 128 and 256 points).  ACA phase before and after: N = 200003
 // 3-d BF16 eps 3e-3 32.0 -> 14.3 ms, N = 100003 3-d FP32 eps 1e-5 53 -> 27 ms,
 // N = 2^20 2-d FP32 33.0 -> 29.5 ms, N = 2^19 2-d FP64 33.5 -> 27.6 ms, N = 4096
 // 2-d FP64 0.69 -> 0.43 ms.
