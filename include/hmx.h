@@ -177,7 +177,7 @@ typedef struct {
                                 U and as its mirror's V) */
     /* Optional device allocator (both NULL: the library's own, which keeps
      * released blocks in a process-wide cache for later builds, as long as
-     * 4 GiB of the device stay free beside them; hmx_trim empties it).  When dev_alloc is set, every device buffer of this build
+     * some of the device stays free beside them; hmx_trim empties it).  When dev_alloc is set, every device buffer of this build
      * and of the handle's later calls (hmx_autotune's scratch vectors,
      * hmx_cg_solve's work vectors) is obtained as dev_alloc(bytes, alloc_ctx)
      * (bytes a multiple of 256; the memory must be device memory of the

@@ -13,17 +13,17 @@
 // allocators ask the driver directly and cannot have them given back.  A
 // process that had held three FP64 handles of 40-50 GB kept all but some MB of
 // the card in idle blocks, and its next kernel with a private segment aborted
-// the queue (out of resources).  So whenever large blocks are kept, kReserve
-// bytes of the device are free: a miss gives idle blocks back until the request
-// and the reserve fit, and so does a large block that comes back while the
-// reserve is not free.  Blocks that the last kRecent allocations passed over go
-// first, the oldest before others (a program that has moved on to other sizes
-// loses the blocks of the earlier ones and keeps its own), then the smallest
-// that covers what is missing, else the largest.  Either rule alone has the
-// program map its own blocks anew in every pass: the best fit unmaps the pass's
-// scratch while the blocks of earlier handles stay (a build of N = 2^20 points
-// 3.8 s instead of 63 ms), the oldest first more than is missing, and what the
-// next step needs, once all blocks are of the running pass.
+// the queue (out of resources).  So while large blocks are kept, kReserve bytes of
+// the device are free as long as blocks can go that the last kRecent allocations
+// passed over, and kFloor bytes whatever goes: a miss gives idle blocks back until
+// the request fits beside them, and so does a large block that comes back.
+// The blocks passed over go first, the oldest before others (a program that has
+// moved on to other sizes loses the blocks of the earlier ones and keeps its
+// own), then the smallest that covers what is missing, else the largest.  Either
+// rule alone has the program map its own blocks anew in every pass: the best fit
+// unmaps the pass's scratch while the blocks of earlier handles stay (a build of
+// N = 2^20 points 3.8 s instead of 63 ms), the oldest first more than is missing,
+// and what the next step needs, once all blocks are of the running pass.
 //
 // Blocks enter the cache only after the work using them has completed (the
 // build synchronises its stream before releasing scratch, destroy
@@ -43,9 +43,14 @@ namespace hmx {
 template <typename Driver>
 class BlockCache {
    public:
-    // room for private segments on every queue (8192 waves of 64 lanes: 0.1 GB
-    // at 200 bytes a lane), the runtime's own buffers and small tensors
-    static constexpr size_t kReserve = (size_t)4 << 30;
+    // room for a kernel's private segments (8192 waves of 64 lanes: 1 GB at 2 KB a
+    // lane), the runtime's own buffers and small tensors
+    static constexpr size_t kReserve = (size_t)2 << 30;
+    // what stays free where every block is of the running passes (the library's own
+    // kernels have no private memory).  A learned BF16 build of N = 2^22 points takes
+    // 303 GB of the card's 309 at its peak, beside 4.3 of torch: its second pass takes
+    // 0.45 s with its own blocks, 2.7 to 4.9 s where the reserve unmaps some
+    static constexpr size_t kFloor = (size_t)256 << 20;
     // a block of at least this size looks at the free memory when it comes
     // back (smaller ones do not move the reserve)
     static constexpr size_t kLarge = (size_t)64 << 20;
@@ -78,7 +83,7 @@ class BlockCache {
                 idle_.erase(it);
                 return true;
             }
-            make_room(dev, *bytes + kReserve);
+            make_room(dev, *bytes);
         }
         bool ok = drv_.alloc(p, *bytes, oom);
         if (!ok && *oom) {
@@ -104,7 +109,7 @@ class BlockCache {
         if (owned_.count(p) == 0) return;
         idle_.insert({bytes, Block{dev, p, clock_}});
         cached_ += bytes;
-        if (bytes >= kLarge) make_room(dev, kReserve);
+        if (bytes >= kLarge) make_room(dev, 0);
     }
 
     // every idle block of every device back to the driver; their bytes
@@ -137,14 +142,15 @@ class BlockCache {
     };
     using Idle = std::multimap<size_t, Block>;  // by size
 
-    // large idle blocks of dev back to the driver until `want` bytes are free or
-    // none is left
-    void make_room(int dev, size_t want) {
+    // large idle blocks of dev back to the driver until `bytes` and what has to stay
+    // free beside them are, or none is left that may go
+    void make_room(int dev, size_t bytes) {
         if (idle_.empty()) return;
         size_t fr = 0;
-        if (!drv_.free_bytes(&fr) || fr >= want) return;
+        if (!drv_.free_bytes(&fr) || fr >= bytes + kReserve) return;
         bool any = false;
-        while (fr < want) {
+        while (fr < bytes + kReserve) {
+            const size_t missing = fr < bytes + kFloor ? bytes + kFloor - fr : 0;
             auto pick = idle_.end();
             bool old = false, covers = false;
             for (auto it = idle_.lower_bound(kLarge); it != idle_.end(); ++it) {  // by size
@@ -152,9 +158,9 @@ class BlockCache {
                 if (clock_ - it->second.since > kRecent) {
                     if (!old || it->second.since < pick->second.since) pick = it;
                     old = true;
-                } else if (!old && !covers) {
+                } else if (missing > 0 && !old && !covers) {
                     pick = it;
-                    covers = it->first >= want - fr;
+                    covers = it->first >= missing;
                 }
             }
             if (pick == idle_.end()) break;

@@ -1676,7 +1676,7 @@ void stage_factors(hmx_hmatrix_s* h, const AcaPlan& plan, hipStream_t st,
         if (keep && !aca_keep.from.alloc) {
             size_t fr = 0, tot = 0;
             check(hipMemGetInfo(&fr, &tot), "memory info");
-            keep = fr + cache().cached() >= ubytes + DeviceCache::kReserve;
+            keep = fr + cache().cached() >= ubytes + ((size_t)4 << 30);
         }
         if (!keep) aca_keep.release();
         alloc(h->upool, ubytes, "factor pool");
